@@ -119,7 +119,9 @@ sw_status sw_layout_query(sw_grid grid, sw_dtype dtype, sw_layout *out);
 /* Create a solver context for one grid (problem statement: grid, halo, g, dx).
  * opts may be NULL: SW_F32, reflective walls, paper scheme, dy = dx, cfl 0.5.
  * halo must be {1, 1, 1, 1} (the width the scheme needs), else SW_ENOTSUP.
- * Allocates a few hundred bytes of device memory on the current device.
+ * Allocates device memory on the current device: a few kilobytes, and for
+ * grids that sw_step advances in one launch (see there) about an eighth of
+ * one buffer more.
  * Errors: SW_EINVAL (shape, g <= 0, dx <= 0, cfl/dt_fixed not exactly one
  * positive, unknown enum), SW_ENOTSUP, SW_ENOMEM, SW_EHIP. */
 sw_status sw_create(sw_grid grid, sw_halo halo, double g, double dx, const sw_opts *opts, sw_ctx **out);
@@ -138,6 +140,13 @@ sw_status sw_fill_halo(sw_ctx *ctx, const sw_state *state, void *stream);
  * entry is ignored (it is refilled first).  A step that produces h <= 0 or a
  * non-finite value sets the context's sticky unstable flag (reported by
  * sw_sync_status); the run continues on garbage.
+ * With the default tuning (or a fused shape that sw_autotune picked), a grid
+ * whose state fits the registers of the device (about 5 million cells in
+ * SW_F32, 2 million in SW_F64) is advanced by one launch for the whole call,
+ * its state held on chip; buf[cur ^ 1] is then left as it was unless nsteps is
+ * odd.  Otherwise, and on a stream under capture, one launch per step.  The
+ * results are bitwise the same.  Launches of the first kind wait for each
+ * other where they would not fit the device together, also across streams.
  * Errors (synchronous): SW_EINVAL, SW_EHIP, SW_ENOMEM (workspace of
  * variant 4 or 5), SW_ENOTSUP (a variant the options exclude). */
 sw_status sw_step(sw_ctx *ctx, sw_state *state, int32_t nsteps, void *stream);
@@ -259,7 +268,8 @@ sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per_trial, con
  * options and scheme, either scheme), all advanced together.  Each grid
  * keeps its own CFL dt, simulated time and sticky flag; a grid advanced in a
  * batch is bitwise identical to the same grid advanced alone with the same
- * launch shape.  One kernel launch per time step covers every grid (a tile
+ * launch shape.  Most batches advance in one launch per call (see
+ * sw_batch_step); otherwise one kernel launch per time step covers every grid (a tile
  * table over all grids; two launches per step, one per chain of grids, for
  * batches of 4 M cells or more); sw_batch_step replays the whole call as
  * hipGraph launches (captured on first use per (nsteps, buffer, tuning)).
@@ -286,7 +296,10 @@ sw_status sw_batch_view(const sw_batch *batch, int32_t i, sw_state *view, sw_lay
 /* Async: materialise every grid's halo of the current buffer. */
 sw_status sw_batch_fill_halo(sw_batch *batch, void *stream);
 /* Async: advance every grid by nsteps (>= 0); the current buffer flips
- * when nsteps is odd.  A batch of 4 M cells or more per step advances as
+ * when nsteps is odd.  With the default tuning (or the batch autotuner's)
+ * most batches advance in one launch for the whole call, each grid held on
+ * chip while it is stepped, largest grids first (as sw_step; bitwise the same
+ * results).  Otherwise a batch of 4 M cells or more per step advances as
  * two chains of grids, the second on a stream the batch owns (default
  * priority), forked from `stream` after the call's first launches and joined
  * back into it at the end: work enqueued on `stream` afterwards sees the

@@ -13,6 +13,7 @@
 
 #include "../../include/sw.h"
 #include "sw_internal.h"
+#include "sw_resident.h"
 
 struct sw_ctx {
     sw_grid grid;
@@ -37,6 +38,15 @@ struct sw_ctx {
     // allocated by the first sw_step that needs it, freed by sw_destroy
     void *ws = nullptr;
     size_t ws_bytes = 0;
+    // the resident time loop, where the grid fits the device (res_ok): its cut,
+    // exchange words and control (behind the scalars, in the same block)
+    bool res_ok = false;
+    bool searched = false;   // the tuning is the autotuner's choice
+    int64_t patience = kResPatience;
+    SwResPlan res{};
+    int cus = 0;
+    unsigned long long *res_words = nullptr;
+    SwResCtl *res_ctl = nullptr;
     double *diag = nullptr;   // partials and result of sw_diagnostics (allocated by sw_create)
 };
 
@@ -254,6 +264,44 @@ void drop_graphs(sw_ctx *ctx) {
     ctx->graphs.clear();
 }
 
+// Whether this call runs as one resident launch: the default tuning or a
+// fused shape that the autotuner picked (one set by the caller is run as
+// asked), a grid that fits the device, and a stream that is not being captured.
+bool resident_call(const sw_ctx *ctx, hipStream_t s) {
+    static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
+    if (!ctx->res_ok) return false;
+    if (!(ctx->searched && ctx->tuning.variant == 2) && std::memcmp(&ctx->tuning, &dflt, sizeof dflt) != 0) return false;
+    return !sw_res_capturing(s);
+}
+
+sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStream_t s) {
+    SwResArgs a{};
+    a.one = ctx->res.team;
+    const int64_t eb = ctx->layout.elem_bytes;
+    for (int b = 0; b < 2; ++b)
+        for (int k = 0; k < 3; ++k) a.plane[b][k] = (char *)state->plane[b][k] + ctx->layout.origin * eb;
+    a.sc = ctx->sc;
+    a.words = ctx->res_words;
+    a.ctl = ctx->res_ctl;
+    a.cur = state->cur;
+    a.nsteps = nsteps;
+    a.bc_x = (int32_t)ctx->opts.bc_x;
+    a.bc_y = (int32_t)ctx->opts.bc_y;
+    a.g = ctx->g;
+    a.dx = ctx->dx;
+    a.dy = ctx->dy;
+    a.cfl = ctx->opts.cfl;
+    a.dt_fixed = ctx->opts.dt_fixed;
+    a.rdx = sw_res_exact_inverse(ctx->dx);
+    a.rdy = sw_res_exact_inverse(ctx->dy);
+    a.poll_first = kResPollFirst;
+    a.patience = ctx->patience;
+    SW_HIP(sw_res_launch_admitted(a, (int)ctx->opts.dtype, (int)ctx->opts.scheme, ctx->res.rows,
+                                  ctx->res.exact, ctx->res.nw,
+                                  ctx->res.team.nwg, ctx->device, ctx->cus, s));
+    return SW_OK;
+}
+
 }  // namespace
 
 sw_status sw_ctx_describe(const sw_ctx *ctx, sw_grid *grid, sw_opts *opts, sw_layout *layout, void **scalars,
@@ -348,8 +396,20 @@ sw_status sw_create(sw_grid grid, sw_halo halo, double g, double dx, const sw_op
     c->layout = lay;
     c->tuning = sw_tuning{0, 0, 0, 0, 0, 0};
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess) e = hipMalloc((void **)&c->sc, sizeof(SwScalars));
-    if (e == hipSuccess) e = hipMemset(c->sc, 0, sizeof(SwScalars));
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    // one block: the scalars, and for the resident loop its control and words
+    const size_t sc_bytes = (sizeof(SwScalars) + 255) / 256 * 256;
+    size_t bytes = sc_bytes;
+    if (e == hipSuccess) {
+        c->res_ok = sw_res_plan((int)o.dtype, grid.nx, grid.ny, lay.pitch, c->cus, &c->res);
+        if (c->res_ok) bytes += 256 + (size_t)c->res.nwords * 8;
+        e = hipMalloc((void **)&c->sc, bytes);
+    }
+    if (e == hipSuccess) e = hipMemset(c->sc, 0, bytes);
+    if (e == hipSuccess && c->res_ok) {
+        c->res_ctl = (SwResCtl *)((char *)c->sc + sc_bytes);
+        c->res_words = (unsigned long long *)((char *)c->sc + sc_bytes + 256);
+    }
     if (e == hipSuccess) e = hipMalloc((void **)&c->diag, sw_diag_scratch_bytes());
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -461,6 +521,7 @@ sw_status sw_set_variant(sw_ctx *ctx, int32_t variant) {
     sw_status st = resolve_tuning(ctx, t, &r);
     if (st != SW_OK && st != SW_ENOTSUP) return st;
     ctx->tuning = t;
+    ctx->searched = false;
     return SW_OK;
 }
 
@@ -470,6 +531,7 @@ sw_status sw_set_tuning(sw_ctx *ctx, const sw_tuning *tuning) {
     sw_status st = resolve_tuning(ctx, *tuning, &r);
     if (st != SW_OK) return st;
     ctx->tuning = *tuning;
+    ctx->searched = false;
     return SW_OK;
 }
 
@@ -500,6 +562,11 @@ sw_status sw_step(sw_ctx *ctx, sw_state *state, int32_t nsteps, void *stream) {
     if (nsteps == 0) return SW_OK;
     if ((st = use_device(ctx)) != SW_OK) return st;
     hipStream_t s = (hipStream_t)stream;
+    if (resident_call(ctx, s)) {
+        if ((st = resident_steps(ctx, state, nsteps, s)) != SW_OK) return st;
+        state->cur ^= (nsteps & 1);
+        return SW_OK;
+    }
     SwTuning tun;
     if ((st = resolve_tuning(ctx, ctx->tuning, &tun)) != SW_OK) return st;
     const size_t need = workspace_bytes(ctx, tun.variant);
@@ -593,6 +660,14 @@ sw_status sw_reset_time(sw_ctx *ctx, void *stream) {
 }  // extern "C"
 
 bool sw_ctx_use_graph(const sw_ctx *ctx) { return ctx && ctx->use_graph; }
+
+void sw_ctx_set_searched(sw_ctx *ctx, bool searched) { ctx->searched = searched; }
+bool sw_ctx_searched(const sw_ctx *ctx) { return ctx->searched; }
+
+// For the tests of the resident loop's way out (not in sw.h): the 100 MHz
+// ticks a workgroup of this context waits for its team; below 0 it does not
+// wait at all, so that the team always gives up.
+extern "C" void sw_internal_ctx_patience(sw_ctx *ctx, long long ticks) { ctx->patience = ticks; }
 
 void sw_ctx_drop_graphs(sw_ctx *ctx) {
     if (ctx) drop_graphs(ctx);

@@ -1,0 +1,248 @@
+// Host side of the resident time loop: how a grid is cut up, and the
+// admission of its launches.
+//
+// The workgroups of a team wait for each other, so all of them have to be
+// resident at once.  Two things see to that.  (1) A grid is cut into at most
+// one workgroup per compute unit, and a launch is held back (by an event
+// wait on its stream) until the resident launches before it that this
+// process still has in flight leave it that many compute units.  Other
+// kernels on the device only delay a team: they end by themselves.  A batch
+// launches more workgroups than fit: workgroups start in order of their
+// index (on each XCD), so the teams of the lowest indices are complete first
+// and end, and so on.  (2) Where a team does not come together all the same
+// (another process holds the device), its workgroups give up together
+// before anything is written and the last of them does the steps alone.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <deque>
+#include <mutex>
+#include <numeric>
+#include <vector>
+
+#include "sw_resident.h"
+
+bool sw_res_cut(int dtype, int nx, int ny, int64_t pitch, int nw, int max_rows, int max_wg, bool spread, SwResPlan *out) {
+    SwResPlan p{};
+    SwResTeam &t = p.team;
+    t.nx = nx;
+    t.ny = ny;
+    t.pitch = pitch;
+    t.ns = (nx + kResStrip - 1) / kResStrip;
+    t.ws = (nx + t.ns - 1) / t.ns;
+    t.ns = (nx + t.ws - 1) / t.ws;
+    const int64_t waves = ((int64_t)ny + max_rows - 1) / max_rows;      // (each with as many rows, give or take one)
+    const int64_t nb = (waves + nw - 1) / nw;
+    if (nb * t.ns > max_wg) return false;
+    t.waves = (int)(spread ? std::min<int64_t>(nb * nw, ny) : waves);
+    t.base = ny / t.waves;
+    t.rem = ny - t.base * t.waves;
+    t.nb = (t.waves + nw - 1) / nw;
+    t.nwg = t.nb * t.ns;
+    p.rows = t.base + (t.rem ? 1 : 0);
+    if (spread && !sw_res_has_rows(p.rows)) {                                    // fewer, taller waves of a listed height
+        int r = p.rows;
+        while (r < max_rows && !sw_res_has_rows(r)) ++r;
+        t.waves = (ny + r - 1) / r;
+        t.base = ny / t.waves;
+        t.rem = ny - t.base * t.waves;
+        t.nb = (t.waves + nw - 1) / nw;
+        t.nwg = t.nb * t.ns;
+        p.rows = t.base + (t.rem ? 1 : 0);
+    }
+    p.nw = nw;
+    p.exact = sw_res_has_rows(p.rows);
+    const uint64_t vw = dtype ? 2 : 1;
+    p.nwords = 2ull * kResFlagWords * t.nwg + vw * (12ull * t.nb * nx + 12ull * t.ns * t.waves * p.rows);
+    if (p.nwords > 0x0fffffffull) return false;                        // 32-bit offsets in the kernel
+    if (!sw_res_shape_ok(dtype, p.rows, nw)) return false;
+    *out = p;
+    return true;
+}
+
+// The cut with the least work per step on a CU's busiest SIMD, in rows: the
+// patches' rows and about 1.5 more each for the halo rows and the exchange,
+// times the waves that share the SIMD, which run at 1 / 1.35 and 1 / 1.1 of
+// the rate when there are only one or two of them (measured, us per step,
+// FP32: 512^2 4 waves of 5 rows 3.64, 8 of 3 3.89, 16 of 2 4.00; 768^2 8 of 6
+// 4.46, 16 of 3 4.64, 4 of 18 5.80; 1280^2 16 of 8 7.27, 4 of 28 8.22, 8 of 18
+// 8.41; 1536^2 8 of 20 8.72, 16 of 10 8.86), a tenth more where 16 FP32 waves
+// of 10 rows or more spill (1280^2: 8 of 14 7.25, 16 of 10 8.31; 1800^2: 8 of
+// 32 12.7, 16 of 16 14.7).
+bool sw_res_plan(int dtype, int nx, int ny, int64_t pitch, int cus, SwResPlan *out) {
+    double best = 0.0;
+    bool found = false;
+    for (int nw = 4; nw <= (dtype ? 8 : 16); nw *= 2) {
+        for (int rows = 1; rows <= (dtype || nw > 8 ? kResRows : kResRowsTall); ++rows) {
+            SwResPlan p;
+            if (!sw_res_has_rows(rows) || !sw_res_cut(dtype, nx, ny, pitch, nw, rows, cus, true, &p) || !p.exact) continue;
+            double cost = (nw == 4 ? 1.35 : nw == 8 ? 2.2 : 4.0) * (p.rows + 1.5);
+            if (nw == 16 && p.rows >= kResRoomy) cost *= 1.1;
+            if (!found || cost < best) {
+                *out = p;
+                best = cost;
+                found = true;
+            }
+        }
+    }
+    return found;
+}
+
+// Workgroups of four waves that a CU holds at once.
+static int batch_wgs_per_cu(int dtype, int rows) { return dtype || rows >= kResRoomy ? 2 : 4; }
+
+// All grids of a batch in patches of the same greatest height, four waves to
+// a workgroup, workgroups in order of their grid's size (largest first).
+static bool cut_batch(int dtype, int n, const int *nx, const int *ny, const int64_t *pitch, int nw, int rows, int cus,
+                      const std::vector<int> &order, SwResBatchPlan *out) {
+    SwResBatchPlan &p = *out;
+    const int max_team = cus * batch_wgs_per_cu(dtype, rows);   // a team must find room on the device as a whole
+    p.nw = nw;
+    p.teams.assign(n, SwResTeam{});
+    p.wg_team.clear();
+    p.nwords = 0;
+    p.rows = 1;
+    for (int g : order) {
+        SwResPlan one;
+        if (!sw_res_cut(dtype, nx[g], ny[g], pitch[g], p.nw, rows, max_team, false, &one)) return false;
+        one.team.wg0 = (int32_t)p.wg_team.size();
+        one.team.words = p.nwords;
+        p.teams[g] = one.team;
+        p.nwords += (one.nwords + 31) / 32 * 32;
+        p.wg_team.insert(p.wg_team.end(), (size_t)one.team.nwg, g);
+        if (p.wg_team.size() > (size_t)1 << 26) return false;
+        p.rows = std::max(p.rows, one.rows);
+    }
+    p.exact = dtype ? p.rows <= kResRows && sw_res_has_rows(p.rows) : sw_res_has_rows(p.rows);
+    for (const SwResTeam &t : p.teams) p.exact = p.exact && t.base >= p.rows - 1;
+    return true;
+}
+
+bool sw_res_plan_batch(int dtype, int n, const int *nx, const int *ny, const int64_t *pitch, int cus, SwResBatchPlan *out) {
+    std::vector<int> order(n);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int x, int y) { return (int64_t)nx[x] * ny[x] > (int64_t)nx[y] * ny[y]; });
+    // Time per step (us) of the per-step launches and of the resident loop in
+    // each patch height.  The latter in bins of teams that are resident
+    // together: rows and 1.5 more per wave, times the waves that share a SIMD
+    // at the rate measured for so many, and a step's exchange, which only
+    // other teams of the bin hide.  (Measured, FP32 / FP64, resident against
+    // per-step: 16 grids of 256^2 7.0 / 18.2 us, 256 of 256^2 63 / 87, 60 of
+    // 512^2 58 / 76, 16 of 1024^2 62 / 78; 64 of 256^2 42 / 48 and 4 of
+    // 1024^2 53 / 44 in FP64, whose patches are so low that one such team
+    // fills the device.)
+    int64_t cells = 0;
+    for (int i = 0; i < n; ++i) cells += (int64_t)nx[i] * ny[i];
+    double best = 0.97 * std::max(16.0, 5.0 + (double)cells / (dtype ? 105e3 : 215e3));
+    bool found = false;
+    for (int rows : {1, 2, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40}) {
+        if (rows > (dtype ? kResRows : kResRowsTall)) break;
+        SwResBatchPlan p;
+        if (!cut_batch(dtype, n, nx, ny, pitch, 4, rows, cus, order, &p)) continue;
+        const int64_t slots = (int64_t)cus * batch_wgs_per_cu(dtype, rows);
+        double us = 0.0;
+        int64_t used = 0;
+        int teams = 0;
+        auto close = [&] {
+            static const double at[5] = {0.0, 1.35, 2.2, 3.7, 5.2};
+            us += (dtype ? 0.37 : 0.135) * at[(used + cus - 1) / cus] * (p.rows + 1.5) + 2.5 / teams;
+            used = teams = 0;
+        };
+        for (int g : order) {
+            if (used + p.teams[g].nwg > slots) close();
+            used += p.teams[g].nwg;
+            ++teams;
+        }
+        close();
+        if (us < best) {
+            *out = std::move(p);
+            best = us;
+            found = true;
+        }
+    }
+    return found;
+}
+
+bool sw_res_capturing(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+hipError_t sw_res_launch_f32(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
+hipError_t sw_res_launch_f64(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
+hipError_t sw_res_launch_f32_tr(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
+hipError_t sw_res_launch_f64_tr(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
+
+hipError_t sw_res_launch(const SwResArgs &a, int dtype, int scheme, int rows, bool exact, int nw, int nwg, hipStream_t s) {
+    if (nwg < 1 || a.nsteps < 1 || !sw_res_shape_ok(dtype, rows, nw)) return hipErrorInvalidValue;
+    if (dtype) return scheme ? sw_res_launch_f64_tr(a, rows, exact, nw, nwg, s) : sw_res_launch_f64(a, rows, exact, nw, nwg, s);
+    return scheme ? sw_res_launch_f32_tr(a, rows, exact, nw, nwg, s) : sw_res_launch_f32(a, rows, exact, nw, nwg, s);
+}
+
+namespace {
+
+// The resident launches in flight on each device: compute units each may
+// hold, and an event recorded behind it.  At most kInFlight are kept; they
+// are dropped when done, or when a later launch has been ordered behind them.
+constexpr size_t kInFlight = 16;
+struct Flight {
+    hipEvent_t done;
+    int cus;
+};
+struct Device {
+    std::deque<Flight> flights;
+    std::vector<hipEvent_t> spare;
+};
+std::mutex g_mutex;
+std::vector<Device> &devices() {
+    static auto *d = new std::vector<Device>();   // never destroyed: the HIP runtime may go first at exit
+    return *d;
+}
+
+}  // namespace
+
+hipError_t sw_res_launch_admitted(const SwResArgs &a, int dtype, int scheme, int rows, bool exact, int nw, int nwg,
+                                  int device, int cus, hipStream_t s) {
+    std::lock_guard<std::mutex> hold(g_mutex);
+    auto &all = devices();
+    if (device < 0) return hipErrorInvalidDevice;
+    if (all.size() <= (size_t)device) all.resize((size_t)device + 1);
+    Device &d = all[(size_t)device];
+    const int want = std::min(nwg, cus);
+    int held = 0;
+    for (const Flight &f : d.flights) held += f.cus;
+    auto retire = [&] {
+        held -= d.flights.front().cus;
+        d.spare.push_back(d.flights.front().done);
+        d.flights.pop_front();
+    };
+    while (!d.flights.empty() && hipEventQuery(d.flights.front().done) == hipSuccess) retire();
+    (void)hipGetLastError();                          // hipErrorNotReady is no error here
+    while (!d.flights.empty() && (held + want > cus || d.flights.size() >= kInFlight)) {
+        hipError_t e = hipStreamWaitEvent(s, d.flights.front().done, 0);
+        if (e != hipSuccess) return e;
+        retire();
+    }
+    hipEvent_t done;
+    if (!d.spare.empty()) {
+        done = d.spare.back();
+        d.spare.pop_back();
+    } else {
+        hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+        if (e != hipSuccess) return e;
+    }
+    hipError_t e = sw_res_launch(a, dtype, scheme, rows, exact, nw, nwg, s);
+    if (e == hipSuccess) e = hipEventRecord(done, s);
+    if (e != hipSuccess) {
+        d.spare.push_back(done);
+        return e;
+    }
+    d.flights.push_back(Flight{done, want});
+    return hipSuccess;
+}

@@ -1,0 +1,6 @@
+// The resident time loop's instances: FP32, transverse scheme (one file each: they build in parallel).
+#include "sw_resident_kernel.h"
+
+hipError_t sw_res_launch_f32_tr(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s) {
+    return launch_rows<float, true>(a, rows, exact, nw, nwg, s);
+}

@@ -78,6 +78,8 @@ sw_status sw_ctx_describe(const sw_ctx *ctx, sw_grid *grid, sw_opts *opts, sw_la
                           size_t *scalars_bytes);
 
 bool sw_ctx_use_graph(const sw_ctx *ctx);
+void sw_ctx_set_searched(sw_ctx *ctx, bool searched);   // the tuning is this search's choice, not the caller's
+bool sw_ctx_searched(const sw_ctx *ctx);
 void sw_ctx_drop_graphs(sw_ctx *ctx);   // the context's captured graphs (none may be in flight)
 
 extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per_trial, const char *cache_path,
@@ -97,6 +99,7 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
 
     sw_tuning best{};
     if (cache_lookup(cache_path, key, &best) && sw_set_tuning(ctx, &best) == SW_OK) {
+        sw_ctx_set_searched(ctx, true);
         if (best_out) sw_get_tuning(ctx, best_out);
         return SW_OK;
     }
@@ -152,6 +155,7 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
 
     sw_tuning prev{};
     sw_get_tuning(ctx, &prev);
+    const bool prev_searched = sw_ctx_searched(ctx);
     // trials replay graphs, as sw_step runs: eager launches would time the
     // host's launch rate on small grids; each shape's two call lengths are
     // captured in an untimed warm-up first
@@ -212,13 +216,16 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
     sw_set_graph(ctx, graph ? 1 : 0);
     if (he != hipSuccess) {
         sw_set_tuning(ctx, &prev);
+        sw_ctx_set_searched(ctx, prev_searched);
         return SW_EHIP;
     }
     if (best_us >= 1e300) {
         sw_set_tuning(ctx, &prev);
+        sw_ctx_set_searched(ctx, prev_searched);
         return SW_ENOTSUP;
     }
     sw_set_tuning(ctx, &best);
+    sw_ctx_set_searched(ctx, true);
     cache_store(cache_path, key, best, best_us);
     if (best_out) sw_get_tuning(ctx, best_out);
     return SW_OK;
