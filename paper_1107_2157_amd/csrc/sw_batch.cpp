@@ -19,6 +19,7 @@
 
 #include "../../include/sw.h"
 #include "sw_batch_internal.h"
+#include "sw_resident.h"
 
 // Shared with sw_api.cpp.
 sw_status sw_fail(sw_status s, const char *fmt, ...);
@@ -51,6 +52,16 @@ struct sw_batch {
     int split = 0;                    // tiles [0, split) step on the call's stream, [split, ntiles) on `side`
     int table_rows = -1, table_vec = -1, table_order = -1;
     bool use_graph = true;
+    // the resident time loop (res_nwg > 0 where it is the faster form): teams,
+    // the workgroups' teams, control and exchange words in one block
+    int res_nwg = 0, res_rows = 0, res_nw = 0, cus = 0;
+    bool res_exact = false;
+    bool searched = false;            // the tuning is the autotuner's choice
+    char *res_mem = nullptr;
+    SwResTeam *res_teams = nullptr;
+    int32_t *res_wg_team = nullptr;
+    SwResCtl *res_ctl = nullptr;
+    unsigned long long *res_words = nullptr;
     uint64_t gen = 0;                 // renewed whenever launch arguments change (bind, tile table)
     hipStream_t cap = nullptr;
     hipStream_t side = nullptr;       // the second chain's stream (default priority)
@@ -268,6 +279,74 @@ sw_status enqueue(const sw_batch *b, const Resolved &r, int nsteps, int cur, hip
     return SW_OK;
 }
 
+// Cut every grid for the resident loop and lay out its tables; res_nwg stays 0
+// where the per-step launches are kept.
+hipError_t build_resident(sw_batch *b) {
+    SwResBatchPlan plan;
+    std::vector<int> nx(b->n), ny(b->n);
+    std::vector<int64_t> pitch(b->n);
+    for (int i = 0; i < b->n; ++i) {
+        nx[i] = b->grids[i].nx;
+        ny[i] = b->grids[i].ny;
+        pitch[i] = b->lay[i].pitch;
+    }
+    if (!sw_res_plan_batch((int)b->opts.dtype, b->n, nx.data(), ny.data(), pitch.data(), b->cus, &plan)) return hipSuccess;
+    const size_t teams = align_up(plan.teams.size() * sizeof(SwResTeam));
+    const size_t wgs = align_up(plan.wg_team.size() * sizeof(int32_t));
+    const size_t ctl = align_up((size_t)b->n * sizeof(SwResCtl));
+    hipError_t e = hipMalloc((void **)&b->res_mem, teams + wgs + ctl + plan.nwords * 8);
+    if (e != hipSuccess) return e;
+    b->res_teams = (SwResTeam *)b->res_mem;
+    b->res_wg_team = (int32_t *)(b->res_mem + teams);
+    b->res_ctl = (SwResCtl *)(b->res_mem + teams + wgs);
+    b->res_words = (unsigned long long *)(b->res_mem + teams + wgs + ctl);
+    e = hipMemcpy(b->res_teams, plan.teams.data(), plan.teams.size() * sizeof(SwResTeam), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(b->res_wg_team, plan.wg_team.data(), plan.wg_team.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset(b->res_ctl, 0, ctl + plan.nwords * 8);
+    if (e != hipSuccess) return e;
+    b->res_rows = plan.rows;
+    b->res_nw = plan.nw;
+    b->res_exact = plan.exact;
+    b->res_nwg = (int)plan.wg_team.size();
+    return hipSuccess;
+}
+
+// Whether a call runs as one resident launch: the default tuning or the
+// autotuner's (a shape set by the caller is run as asked), a batch that is
+// cut for it, and a stream that is not being captured.
+bool resident_call(const sw_batch *b, hipStream_t s) {
+    static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
+    if (!b->res_nwg || (!b->searched && std::memcmp(&b->tuning, &dflt, sizeof dflt) != 0)) return false;
+    return !sw_res_capturing(s);
+}
+
+sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
+    SwResArgs a{};
+    a.teams = b->res_teams;
+    a.wg_team = b->res_wg_team;
+    a.grids = b->d_grids;
+    a.bsc = b->d_sc;
+    a.words = b->res_words;
+    a.ctl = b->res_ctl;
+    a.cur = b->cur;
+    a.nsteps = nsteps;
+    a.bc_x = (int)b->opts.bc_x;
+    a.bc_y = (int)b->opts.bc_y;
+    a.g = b->g;
+    a.dx = b->dx;
+    a.dy = b->dy;
+    a.cfl = b->opts.cfl;
+    a.dt_fixed = b->opts.dt_fixed;
+    a.rdx = sw_res_exact_inverse(b->dx);
+    a.rdy = sw_res_exact_inverse(b->dy);
+    a.poll_first = kResPollFirst;
+    a.patience = kResPatience;
+    BHIP(sw_res_launch_admitted(a, (int)b->opts.dtype, (int)b->opts.scheme, b->res_rows, b->res_exact, b->res_nw,
+                                b->res_nwg, b->device, b->cus, s));
+    return SW_OK;
+}
+
 bool same_tuning(const sw_tuning &x, const sw_tuning &y) { return std::memcmp(&x, &y, sizeof x) == 0; }
 
 sw_status check_bound(const sw_batch *b) {
@@ -355,6 +434,7 @@ int sw_batch_internal_clone(const sw_batch *src, sw_batch **out, void **arena) {
     sw_status st = sw_batch_create(src->n, src->grids.data(), halo, src->g, src->dx, &src->opts, &c);
     if (st != SW_OK) return st;
     c->tuning = src->tuning;
+    c->searched = src->searched;
     hipError_t e = hipMalloc(arena, 2 * c->region);
     if (e != hipSuccess) {
         sw_batch_destroy(c);
@@ -419,6 +499,8 @@ sw_status sw_batch_create(int32_t n, const sw_grid *grids, sw_halo halo, double 
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device);
+    if (e == hipSuccess) e = build_resident(b);
     if (e != hipSuccess) {
         sw_batch_destroy(b);
         return sw_fail(e == hipErrorOutOfMemory ? SW_ENOMEM : SW_EHIP, "batch_create: %s", hipGetErrorString(e));
@@ -437,6 +519,7 @@ sw_status sw_batch_destroy(sw_batch *b) {
     if (b->d_sc) (void)hipFree(b->d_sc);
     if (b->d_grids) (void)hipFree(b->d_grids);
     if (b->d_tiles) (void)hipFree(b->d_tiles);
+    if (b->res_mem) (void)hipFree(b->res_mem);
     delete b;
     return SW_OK;
 }
@@ -495,6 +578,7 @@ sw_status sw_batch_set_tuning(sw_batch *b, const sw_tuning *t) {
     if (st != SW_OK) return st;
     const bool had = resolve(b, b->tuning, &prev) == SW_OK;
     b->tuning = *t;
+    b->searched = false;
     // any change of the launch shape renews the generation, so rollouts
     // captured by a surrogate with the old shape are captured anew (the tile
     // table below renews it too when rows, vec or order change)
@@ -543,7 +627,9 @@ sw_status sw_batch_step(sw_batch *b, int32_t nsteps, void *stream) {
     if ((st = resolve(b, b->tuning, &r)) != SW_OK) return st;
     if ((st = build_tiles(b, r)) != SW_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    if (!b->use_graph) {
+    if (resident_call(b, s)) {
+        if ((st = resident_steps(b, nsteps, s)) != SW_OK) return st;
+    } else if (!b->use_graph) {
         if ((st = enqueue(b, r, nsteps, b->cur, s)) != SW_OK) return st;
     } else {
         const bool two = split_table(b);
@@ -689,6 +775,7 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
             }
         }
         if (found && sw_batch_set_tuning(b, &hit) == SW_OK) {
+            b->searched = true;
             if (best_out) sw_batch_get_tuning(b, best_out);
             return SW_OK;
         }
@@ -705,6 +792,7 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
                         for (int order = 0; order <= 2; ++order) cands.push_back(sw_tuning{2, rows, vecs[vi], occ, pd, order});
     const bool graph0 = b->use_graph;
     const sw_tuning prev = b->tuning;
+    const bool prev_searched = b->searched;
     const int cur0 = b->cur;
     void *backup = nullptr, *sbackup = nullptr;
     const size_t sbytes = (size_t)b->n * sizeof(SwBatchScalars);
@@ -786,10 +874,12 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
     b->use_graph = graph0;
     if (he != hipSuccess || best_us >= 1e300) {
         sw_batch_set_tuning(b, &prev);
+        b->searched = prev_searched;
         return he != hipSuccess ? sw_fail(SW_EHIP, "batch_autotune: %s", hipGetErrorString(he))
                                 : sw_fail(SW_ENOTSUP, "batch_autotune: no candidate ran");
     }
     sw_batch_set_tuning(b, &best);
+    b->searched = true;
     if (cache_path && *cache_path) {
         std::ofstream f(cache_path, std::ios::app);
         f << key << " " << best.variant << " " << best.rows << " " << best.vec << " " << best.occupancy << " "
