@@ -63,6 +63,25 @@ struct SwNetFusedArgs {
 };
 hipError_t sw_net_fused(const SwNetFusedArgs &a, hipStream_t s);
 void sw_net_fused_tile(int B, int H, int W, int *th, int *tw);
+// Two layers in one launch (sw_pair.hip): FIRST, the first layer (from x, 8
+// channels, or from a batch's planes if grids is set) and a residual block;
+// MIDDLE, two residual blocks; OUT, a residual block and the output layer.
+enum { SW_PAIR_FIRST = 0, SW_PAIR_MIDDLE = 1, SW_PAIR_OUT = 2 };
+struct SwPairArgs {
+    const void *x;                 // BF16 NHWC input with halo (null with grids)
+    const void *wa, *wb;           // forward weights of the two layers
+    const float *ba, *bb;          // biases
+    void *ya, *yb;                 // outputs, BF16 NHWC with halo (ya may be null)
+    void *ra, *rb;                 // ReLU parts of the residual blocks (may be null)
+    float *yf, *yf2;               // OUT: FP32 [B][H][W][4], and a second copy (may be null)
+    double *dh_part;               // OUT: per-row sums of channel 0 as SwConvArgs::dh_part (may be null)
+    const SwBatchGrid *grids;      // FIRST: planes of buffer cur, normalised by nrm
+    SwGateStats *clear_stats;      // FIRST with grids: the jump's gate statistics, cleared per grid (may be null)
+    int cur, B, H, W;
+    SwNorm nrm;
+};
+bool sw_conv_pair_fits(int H, int W);   // W at most 256
+hipError_t sw_conv_pair(const SwPairArgs &a, int pair, hipStream_t s);
 // Compute units of the current device (for persistent grids).
 int sw_device_cus();
 

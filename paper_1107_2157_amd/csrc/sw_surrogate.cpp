@@ -112,6 +112,18 @@ SwConvArgs conv_args(const sw_net *n, int B, const void *x) {
     return a;
 }
 
+// Whether the forward pass runs two layers a launch: images up to 256 wide
+// (a cap on the workgroups of the single-layer kernels asks for those), and
+// where the launch's step after step of rows is not what takes the time: at
+// widths of 192 and 256 from 200 000 pixels on.  Measured, forward pass of
+// two layers a launch against one: 64 grids of 256^2 482 / 596 us, 8 92 / 111,
+// 4 67 / 71, 1 55 / 48; 3 of 33x192 50 / 45; 2 of 40x128 39 / 44; one of 64^2
+// 36 / 42.  A rollout of 32 grids of 256^2 (64 steps): 2.18 / 3.09 ms.
+bool use_pairs(const sw_net *n, int B) {
+    if (n->block_cap != 0 || !sw_conv_pair_fits(n->H, n->W)) return false;
+    return n->W <= 128 || (int64_t)B * n->H * n->W >= 200000;
+}
+
 // X0 -> act[0..4] -> delta; with train, also the ReLU parts (backward masks).
 // With `planes` (a rollout) the first layer reads the batch's buffer directly
 // (normalising it and clearing the jump's gate statistics) instead of X0, and
@@ -121,7 +133,43 @@ struct RolloutInput {
     int cur;
     bool dh_sums;
 };
-sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const RolloutInput *planes = nullptr) {
+// delta (optional): a second copy of the prediction.  With two layers a
+// launch (use_pairs) a rollout leaves the activations between them unwritten.
+sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const RolloutInput *planes = nullptr,
+                  float *delta = nullptr) {
+    if (use_pairs(n, B)) {
+        for (int l = 0; l < kLayers; l += 2) {
+            const SwLayerDesc &La = n->L[l], &Lb = n->L[l + 1];
+            SwPairArgs a{};
+            a.x = l == 0 ? n->x0 : n->act[l - 1];
+            a.wa = La.wk;
+            a.wb = Lb.wk;
+            a.ba = n->master + La.b_off;
+            a.bb = n->master + Lb.b_off;
+            a.ya = planes ? nullptr : n->act[l];
+            if (train && residual(l)) a.ra = n->relu[l - 1];
+            if (l + 1 < kLayers - 1) {
+                a.yb = n->act[l + 1];
+                if (train) a.rb = n->relu[l];
+            } else {
+                a.yf = n->delta;
+                a.yf2 = delta;
+                if (planes && planes->dh_sums) a.dh_part = n->dh_part;
+            }
+            if (l == 0 && planes) {
+                a.x = nullptr;
+                a.grids = planes->grids;
+                a.cur = planes->cur;
+                a.nrm = n->nrm;
+                a.clear_stats = n->stats;
+            }
+            a.B = B;
+            a.H = n->H;
+            a.W = n->W;
+            SHIP(sw_conv_pair(a, l == 0 ? SW_PAIR_FIRST : l + 2 == kLayers ? SW_PAIR_OUT : SW_PAIR_MIDDLE, s));
+        }
+        return SW_OK;
+    }
     for (int l = 0; l < kLayers; ++l) {
         const SwLayerDesc &L = n->L[l];
         SwConvArgs a = conv_args(n, B, l == 0 ? n->x0 : n->act[l - 1]);
@@ -149,6 +197,7 @@ sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const Rollo
         }
         SHIP(sw_conv3x3(a, L.cinp, L.cout, mode, s));
     }
+    if (delta) SHIP(hipMemcpyAsync(delta, n->delta, (size_t)B * n->H * n->W * 16, hipMemcpyDeviceToDevice, s));
     return SW_OK;
 }
 
@@ -370,9 +419,7 @@ sw_status sw_surrogate_forward(sw_net *n, const float *u, int32_t B, float *delt
     if (!u) return sw_fail(SW_EINVAL, "surrogate_forward: NULL input");
     hipStream_t s = (hipStream_t)stream;
     SHIP(sw_sur_prep_dense(u, nullptr, B, n->H, n->W, n->cfg.bc_x, n->cfg.bc_y, n->nrm, n->x0, nullptr, s));
-    if ((st = forward(n, B, false, s)) != SW_OK) return st;
-    if (delta) SHIP(hipMemcpyAsync(delta, n->delta, (size_t)B * n->H * n->W * 16, hipMemcpyDeviceToDevice, s));
-    return SW_OK;
+    return forward(n, B, false, s, nullptr, delta);
 }
 
 sw_status sw_surrogate_activation(sw_net *n, int32_t layer, const void **ptr, int64_t *bytes) {
