@@ -879,9 +879,13 @@ hipError_t sw_sur_apply(const float *delta, const double *dh_part, int nparts, c
                         SwApplyPart *part, unsigned *ticket, hipStream_t s) {
     if (project && (!dh_part || nparts < 1)) return hipErrorInvalidValue;
     if (!part || !ticket) return hipErrorInvalidValue;
-    // at most 128 blocks per grid (two pixels per thread on a 256^2 grid):
-    // the blocks of one grid meet on its ticket
-    dim3 grid(std::min(per_grid_blocks((int64_t)H * W, B), 128u), B);
+    // at most 128 blocks per grid (two pixels per thread on a 256^2 grid), and
+    // few more than two per CU in all: a block's three exchanges and its
+    // ticket, performed in memory, take longer than its pixels (32 grids of
+    // 256^2, a 64-step rollout: 128 blocks per grid 2235 us, 64 2090, 32 1982,
+    // 16 1960; 64 grids 3927 with 128, 3592 with 32, 3620 with 8)
+    const unsigned most = std::max(8u, std::min(128u, 512u / (unsigned)B));
+    dim3 grid(std::min(per_grid_blocks((int64_t)H * W, B), most), B);
     k_apply<<<grid, 256, 0, s>>>(delta, dh_part, nparts, grids, cur, H, W, nrm, project, bcx, bcy, st, part, ticket);
     return hipGetLastError();
 }
