@@ -14,14 +14,15 @@ struct SwNorm {
 
 // One 3x3 convolution launch (see sw_conv.hip for layouts).  Modes:
 //   RELU:  y = relu(conv(x) + b)                                (first layer)
-//   RESID: y = x + relu(conv(x) + b), y2 = relu(conv(x) + b)     (residual blocks)
+//   RESID: y = x + relu(conv(x) + b)                             (residual blocks)
 //   F32:   yf = conv(x) + b in FP32                              (output layer)
-//   DGRAD: G = conv(x) + add, y = G, y2 = G where mask > 0       (input gradient)
+//   DGRAD: G = conv(x) + add, y = G, y2 = G where mask is set    (input gradient)
 //   RELU_PLANES: RELU with the input read from the FP32 planes of a batch of
 //          grids (buffer cur, ghosts materialised) and normalised on the fly
 //          (the rollout's first layer); the tile at a grid's origin also
 //          clears that grid's gate statistics (clear_stats).
-// Every BF16 output may be null except y in RELU / RESID and y2 in DGRAD.
+// RELU and RESID also write the mask of their ReLU where mask is set (B H W
+// words, sw_conv_dev.h).  y may be null in DGRAD.
 // F32 with dh_part set also writes, per grid and output row, the sum of the
 // row's channel-0 outputs (FP64, fixed order) at dh_part[b * H + y].
 struct SwConvArgs {
@@ -29,10 +30,10 @@ struct SwConvArgs {
     const void *w;       // BF16 [COUT padded to 16][K padded to 32] implicit-GEMM weights
     const float *bias;   // FP32 [COUT] (RELU, RESID and F32 modes)
     void *y;             // BF16 NHWC output with halo, COUT channels
-    void *y2;            // BF16 NHWC output with halo, COUT channels (RESID: relu part, DGRAD: masked)
+    void *y2;            // BF16 NHWC output with halo, COUT channels (DGRAD: masked)
     float *yf;           // FP32 [B][H][W][4] output (F32 mode)
     const void *add;     // BF16 NHWC with halo, COUT channels, added before rounding (DGRAD)
-    const void *mask;    // BF16 NHWC with halo, COUT channels: y2 kept where mask > 0 (DGRAD)
+    unsigned *mask;      // where the layer's ReLU is positive (written by RELU, RESID: may be null; read by DGRAD)
     int B, H, W;
     int max_blocks;      // cap on the persistent grid (0: one block per resident slot)
     const SwBatchGrid *grids;   // RELU_PLANES: the batch's grids (all H x W)
@@ -72,7 +73,7 @@ struct SwPairArgs {
     const void *wa, *wb;           // forward weights of the two layers
     const float *ba, *bb;          // biases
     void *ya, *yb;                 // outputs, BF16 NHWC with halo (ya may be null)
-    void *ra, *rb;                 // ReLU parts of the residual blocks (may be null)
+    unsigned *ma, *mb;             // masks of the two layers' ReLUs (sw_conv_dev.h; may be null; not of the output layer)
     float *yf, *yf2;               // OUT: FP32 [B][H][W][4], and a second copy (may be null)
     double *dh_part;               // OUT: per-row sums of channel 0 as SwConvArgs::dh_part (may be null)
     const SwBatchGrid *grids;      // FIRST: planes of buffer cur, normalised by nrm
@@ -82,6 +83,16 @@ struct SwPairArgs {
 };
 bool sw_conv_pair_fits(int H, int W);   // W at most 256
 hipError_t sw_conv_pair(const SwPairArgs &a, int pair, hipStream_t s);
+// Two input-gradient layers in one launch (sw_grad.hip), both residual blocks:
+//   Ga = conv(x) + add, za = Ga where ma;  Gb = conv(za) + Ga, zb = Gb where mb, yb = Gb
+struct SwGradPairArgs {
+    const void *x, *add;           // BF16 NHWC with halo, 32 channels
+    const void *wa, *wb;           // input-gradient weights of the two layers
+    const unsigned *ma, *mb;       // masks of the layers below (sw_conv_dev.h)
+    void *za, *zb, *yb;            // BF16 NHWC with halo, 32 channels (yb may be null)
+    int B, H, W;
+};
+hipError_t sw_grad_pair(const SwGradPairArgs &a, hipStream_t s);   // sw_conv_pair_fits
 // Compute units of the current device (for persistent grids).
 int sw_device_cus();
 

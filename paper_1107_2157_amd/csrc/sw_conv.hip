@@ -16,29 +16,19 @@
 // n + 16 * (k / 8), element k % 8; D[m][n] in lane n + 16 * (m / 4), element
 // m % 4.
 #include "sw_conv.h"
+#include "sw_conv_dev.h"
 #include "sw_dma.h"
 
 #include <algorithm>
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int CIN> constexpr int ksteps() { return CIN == 32 ? 9 : 3; }
 
 constexpr int kTileCols = 64;               // output pixels per tile row (4 MFMA N blocks)
 constexpr int kStageCols = kTileCols + 2;   // staged pixels per row (halo)
-
-// Offset (BF16 elements) of 16-byte chunk c (channels 8c .. 8c + 7) of pixel
-// p in an LDS area of 32-channel pixels.  The chunk index is XORed with bits
-// 1-2 of the pixel index.  A ds_read_b128 is served 8 lanes (128 bytes, 32
-// banks) at a time, and 8 lanes of an MFMA operand read the same chunk of 8
-// consecutive pixels: at a plain 64-byte pixel stride those fall on 2 of the
-// 8 bank quads, a 4-way conflict (measured: about 70 % of the convolutions'
-// LDS cycles were bank-conflict cycles); swizzled they cover all 8.
-__device__ __forceinline__ int chunk_off(int p, int c) { return p * 32 + ((c ^ ((p >> 1) & 3)) << 3); }
 
 // Persistent, LDS-staged 3x3 convolution.  Each block owns a contiguous run
 // of ROWS-row x 64-pixel output tiles (ROWS = waves per block), numbered down
@@ -192,7 +182,8 @@ __global__ __launch_bounds__(64 * ROWS, 2) void k_conv3x3(SwConvArgs a, int tile
             } else {
                 // The wave's 64 output pixels x COUT channels are one contiguous run of the
                 // NHWC row: values go to the wave's LDS area, then out as 16 contiguous bytes
-                // per lane.  Two outputs (RESID's ReLU part, DGRAD's dZ) reuse the area in turn.
+                // per lane: chunk lane % 4 of pixels 16 k + lane / 4, those of mask word
+                // 16 (lane % 4) + lane / 4.
                 const int64_t row0 = (((int64_t)b * (a.H + 2) + y + 1) * Wp + x0 + 1) * COUT;
                 // the area holds the wave's 64 pixels x 32 channels, chunks swizzled as the input tile's
                 auto slot = [&](int mb, int pb) -> bf16x4 & {
@@ -203,76 +194,41 @@ __global__ __launch_bounds__(64 * ROWS, 2) void k_conv3x3(SwConvArgs a, int tile
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 };
-                auto flush = [&](__bf16 *dst) {
+                unsigned *const mw = a.mask + (((int64_t)b * a.H + y) * tiles_x + tx) * 64 + 16 * (lane & 3) + (lane >> 2);
+                auto flush = [&] {
+                    unsigned bits = MODE == SW_CONV_DGRAD ? *mw : 0u;
                     wave_sync();
 #pragma unroll
                     for (int k = 0; k < kTileCols * COUT / 512; ++k) {   // non-temporal: GB-sized tensors
                         const int e = k * 512 + lane * 8;                 // chunk (e / 8) % 4 of pixel e / 32
-                        __builtin_nontemporal_store(
-                            *reinterpret_cast<const bf16x8 *>(&ostage[w][chunk_off(e >> 5, (e >> 3) & 3)]),
-                            reinterpret_cast<bf16x8 *>(dst + row0 + e));
+                        const u32x4 v = *reinterpret_cast<const u32x4 *>(&ostage[w][chunk_off(e >> 5, (e >> 3) & 3)]);
+                        if (MODE != SW_CONV_DGRAD || a.y)
+                            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>((__bf16 *)a.y + row0 + e));
+                        if (MODE == SW_CONV_DGRAD)
+                            __builtin_nontemporal_store(mask_keep(v, bits, k), reinterpret_cast<u32x4 *>((__bf16 *)a.y2 + row0 + e));
+                        else if (MODE == SW_CONV_RELU_BF16)
+                            bits = mask_push(bits, v);
                     }
+                    if (MODE == SW_CONV_RELU_BF16 && a.mask) *mw = bits;
                     wave_sync();   // the copy's reads are done before the area is written again
                 };
-                auto relu_part = [&](int mb, int pb) {
-                    f32x4 v = acc[mb][pb];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q] + a.bias[mb * 16 + 4 * g + q], 0.f);
-                    return v;
-                };
-                if (MODE == SW_CONV_RELU_BF16 || MODE == SW_CONV_RELU_PLANES || MODE == SW_CONV_RESID_BF16) {
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
+                    for (int pb = 0; pb < NPB; ++pb) {
+                        f32x4 v = acc[mb][pb];
+                        if (MODE != SW_CONV_DGRAD) {
 #pragma unroll
-                        for (int pb = 0; pb < NPB; ++pb) {
-                            f32x4 v = relu_part(mb, pb);
-                            if (MODE == SW_CONV_RESID_BF16) {   // CIN == COUT: the block's input at this pixel, from LDS
-                                const bf16x4 xin = *reinterpret_cast<const bf16x4 *>(
-                                    T + chunk_off((w + 1) * kStageCols + pb * 16 + n + 1, 2 * mb + (g >> 1)) + 4 * (g & 1));
+                            for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q] + a.bias[mb * 16 + 4 * g + q], 0.f);
+                        } else if (a.add) {   // G = conv + add into y (if set), dZ = G where the mask is set into y2
+                            const bf16x4 ad = *reinterpret_cast<const bf16x4 *>(
+                                (const __bf16 *)a.add + row0 + (pb * 16 + n) * COUT + mb * 16 + 4 * g);
 #pragma unroll
-                                for (int q = 0; q < 4; ++q) v[q] += (float)xin[q];
-                            }
-                            slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+                            for (int q = 0; q < 4; ++q) v[q] += (float)ad[q];
                         }
-                    flush((__bf16 *)a.y);
-                    if (MODE == SW_CONV_RESID_BF16 && a.y2) {
-#pragma unroll
-                        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                            for (int pb = 0; pb < NPB; ++pb) {
-                                const f32x4 v = relu_part(mb, pb);
-                                slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                            }
-                        flush((__bf16 *)a.y2);
+                        slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
                     }
-                } else {   // SW_CONV_DGRAD: G = conv + add into y (if set), dZ = G where mask > 0 into y2
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int pb = 0; pb < NPB; ++pb) {
-                            f32x4 v = acc[mb][pb];
-                            if (a.add) {
-                                const bf16x4 ad = *reinterpret_cast<const bf16x4 *>(
-                                    (const __bf16 *)a.add + row0 + (pb * 16 + n) * COUT + mb * 16 + 4 * g);
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) v[q] += (float)ad[q];
-                            }
-                            slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                        }
-                    if (a.y) flush((__bf16 *)a.y);
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int pb = 0; pb < NPB; ++pb) {   // each lane rewrites only its own values
-                            const bf16x4 mk = *reinterpret_cast<const bf16x4 *>(
-                                (const __bf16 *)a.mask + row0 + (pb * 16 + n) * COUT + mb * 16 + 4 * g);
-                            bf16x4 gv = slot(mb, pb);
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) gv[q] = (float)mk[q] > 0.f ? gv[q] : (__bf16)0.f;
-                            slot(mb, pb) = gv;
-                        }
-                    flush((__bf16 *)a.y2);
-                }
+                flush();
             }
         }
         if (t + 1 < t1) store_tile(buf ^ 1);                      // buffer buf ^ 1 was last read before the previous barrier
@@ -452,17 +408,10 @@ __global__ __launch_bounds__(64 * ROWS, 1) void k_conv3x3_dma(SwConvArgs a, int 
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 };
-                constexpr int FL = kTileCols * COUT / 512;    // 16-byte stores per lane per output
-                auto flush = [&](__bf16 *dst) {
-                    wave_sync();
-#pragma unroll
-                    for (int k = 0; k < FL; ++k) {
-                        const int e = k * 512 + lane * 8;
-                        __builtin_nontemporal_store(
-                            *reinterpret_cast<const bf16x8 *>(&ostage[w][chunk_off(e >> 5, (e >> 3) & 3)]),
-                            reinterpret_cast<bf16x8 *>(dst + row0 + e));
-                    }
-                    wave_sync();
+                constexpr int FL = kTileCols * COUT / 512;    // 16-byte stores per lane
+                auto staged = [&](int k) {                    // chunk lane % 4 of pixel 16 k + lane / 4
+                    const int e = k * 512 + lane * 8;
+                    return *reinterpret_cast<const u32x4 *>(&ostage[w][chunk_off(e >> 5, (e >> 3) & 3)]);
                 };
                 auto relu_part = [&](int mb, int pb) {
                     f32x4 v = acc[mb][pb];
@@ -481,9 +430,13 @@ __global__ __launch_bounds__(64 * ROWS, 1) void k_conv3x3_dma(SwConvArgs a, int 
                         for (int q = 0; q < 4; ++q) v[q] += (float)xin[q];
                         slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
                     }
-                flush((__bf16 *)a.y);
+                wave_sync();
+#pragma unroll
+                for (int k = 0; k < FL; ++k)
+                    __builtin_nontemporal_store(staged(k), reinterpret_cast<u32x4 *>((__bf16 *)a.y + row0 + k * 512 + lane * 8));
+                wave_sync();
                 stores = FL;
-                if (a.y2) {
+                if (a.mask) {                                 // the ReLU alone goes through the area a second time
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -491,8 +444,13 @@ __global__ __launch_bounds__(64 * ROWS, 1) void k_conv3x3_dma(SwConvArgs a, int 
                             const f32x4 v = relu_part(mb, pb);
                             slot(mb, pb) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
                         }
-                    flush((__bf16 *)a.y2);
-                    stores += FL;
+                    wave_sync();
+                    unsigned bits = 0;
+#pragma unroll
+                    for (int k = 0; k < FL; ++k) bits = mask_push(bits, staged(k));
+                    a.mask[(((int64_t)b * a.H + y) * tiles_x + tx) * 64 + 16 * (lane & 3) + (lane >> 2)] = bits;
+                    wave_sync();
+                    stores += 1;
                 }
             }
         }
@@ -502,7 +460,7 @@ __global__ __launch_bounds__(64 * ROWS, 1) void k_conv3x3_dma(SwConvArgs a, int 
         // 16-byte lane store of a flush, one per f32x4 store, the row sum);
         // the loop issues no other vector memory operation.  A count below
         // the true one only waits longer.
-        if (t + 1 < t1) wait_vm_upto<PERW + (MODE == SW_CONV_F32 ? NPB + 1 : 2 * kTileCols * COUT / 512)>(
+        if (t + 1 < t1) wait_vm_upto<PERW + (MODE == SW_CONV_F32 ? NPB + 1 : kTileCols * COUT / 512 + 1)>(
             (t + 2 < t1 ? nw : 0) + stores);
         __syncthreads();
     }

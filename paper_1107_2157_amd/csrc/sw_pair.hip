@@ -21,6 +21,7 @@
 // with 8 consecutive channels of a pixel: 16-byte stores to LDS and to
 // memory, without a pass through LDS to gather them.
 #include "sw_conv.h"
+#include "sw_conv_dev.h"
 #include "sw_dma.h"
 
 #include <algorithm>
@@ -28,64 +29,10 @@
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Chunk c (channels 8c .. 8c + 7) of pixel p in a row of 32-channel pixels
-// (BF16 elements): the chunk index XORed with pixel bits 1-2, so that the 8
-// lanes of a 128-byte LDS access hit 8 different bank quads.
-__device__ __forceinline__ int chunk_off(int p, int c) { return p * 32 + ((c ^ ((p >> 1) & 3)) << 3); }
-
-__device__ __forceinline__ f32x4 mfma(bf16x8 w, bf16x8 x, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
-}
-
-// 16 bytes at byte offset `at` of the row r; dropped outside it (a row that
-// is not to be stored has length 0, so that a step has no branch around its
-// stores).  Non-temporal: GB-sized tensors.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ rsrc_t row_rsrc(void *row, bool keep, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(row, (short)0, keep ? bytes : 0, 0x00020000);
-}
-template <typename V> __device__ __forceinline__ void store_row(rsrc_t r, int at, const V &v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at, 0, 2);
-}
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 constexpr int kRing = 5;   // input rows in LDS
 
 enum { FIRST_DENSE = 0, FIRST_PLANES = 1, RESID = 2 };   // role a: first layer (8-channel input or planes), residual block
                                                          // role b: residual block, or the output layer (OUT)
-
-// One step of a 32-channel layer: the new row T (LDS) into the accumulators
-// of the rows below (first contribution), beside and above it, a block of 16
-// pixels at a time.  done(pb) is called once block pb's last row is complete
-// and the next block's MFMAs are underway: its vector instructions fill the
-// matrix core's 16 cycles per MFMA (done after all MFMAs, both waves of a
-// SIMD, in step by the barrier, left the matrix cores idle meanwhile).
-template <int MB, int NXT, int MID, int FIN, typename Done>
-__device__ __forceinline__ void conv_row(const __bf16 *T, const int off[3], const bf16x8 (&wt)[9][MB],
-                                         f32x4 (&acc)[3][MB][4], Done &&done) {
-#pragma unroll
-    for (int pb = 0; pb < 4; ++pb) {
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            const bf16x8 xb = *reinterpret_cast<const bf16x8 *>(T + off[dx] + pb * 512);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                acc[FIN][mb][pb] = mfma(wt[6 + dx][mb], xb, acc[FIN][mb][pb]);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                acc[NXT][mb][pb] = mfma(wt[dx][mb], xb, dx == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[NXT][mb][pb]);
-                acc[MID][mb][pb] = mfma(wt[3 + dx][mb], xb, acc[MID][mb][pb]);
-            }
-        }
-        if (pb > 0) done(pb - 1);
-    }
-    done(3);
-}
 
 // relu(acc + bias) of a lane's 8 channels.
 __device__ __forceinline__ void relu8(const f32x4 &lo, const f32x4 &hi, const float bias[8], float v[8]) {
@@ -95,12 +42,8 @@ __device__ __forceinline__ void relu8(const f32x4 &lo, const f32x4 &hi, const fl
         v[4 + q] = fmaxf(hi[q] + bias[4 + q], 0.f);
     }
 }
-__device__ __forceinline__ bf16x8 to_bf16(const float v[8]) {
-    return bf16x8{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3], (__bf16)v[4], (__bf16)v[5], (__bf16)v[6], (__bf16)v[7]};
-}
-
 // MIDS: 0, role a's rows stay on chip; 1, they are stored; 2, they and the
-// residual blocks' ReLU parts (the backward pass's masks) are.
+// backward pass's masks are.
 template <int A, bool OUT, int G, int MIDS>
 __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows, int nseg) {
     constexpr int W = 64 * G, PX = W + 2;
@@ -243,12 +186,12 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
             const bool inside = r >= 0 && r < H, keep = r >= ys && r < ye;   // else zero; else not stored
             const int64_t row = ((img_row + r + 1) * PX + 1) * 64;
             const rsrc_t ry = row_rsrc((char *)a.ya + (MIDS ? row : 0), MIDS && keep, W * 64);
-            const rsrc_t rr = row_rsrc((char *)a.ra + (MIDS == 2 ? row : 0), MIDS == 2 && keep, W * 64);
+            unsigned bits = 0;
             auto done = [&](int pb) {
                 float v[8];
                 relu8(acc[E][0][pb], acc[E][1][pb], bias, v);
+                if (MIDS == 2) bits = mask_push(bits, __builtin_bit_cast(u32x4, to_bf16(v)));
                 if (A == RESID) {
-                    if (MIDS == 2) store_row(rr, (int)px0 * 64 + g * 16 + pb * 1024, to_bf16(v));
                     const bf16x8 xin = *reinterpret_cast<const bf16x8 *>(&in[(s + kRing - 1) % kRing][off[1] + pb * 512]);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) v[q] += (float)xin[q];
@@ -287,8 +230,10 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
                 }
                 done(3);
             }
+            if constexpr (MIDS == 2)
+                store_word(row_rsrc((char *)a.ma + ((int64_t)img * H + r) * W * 4, keep, W * 4), grp * 256 + lane * 4, bits);
             store_planes(s + AHEAD);
-            land(std::integral_constant<int, MIDS == 0 ? 0 : MIDS == 2 && A == RESID ? 8 : 4>{}, s);
+            land(std::integral_constant<int, MIDS == 0 ? 0 : MIDS == 2 ? 5 : 4>{}, s);
         };
         for (int s = 0; s < nsteps; s += 3) {
             step(std::integral_constant<int, 0>{}, s);
@@ -344,18 +289,20 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
             } else {
                 const int64_t row = ((img_row + o + 1) * PX + 1) * 64;
                 const rsrc_t ry = row_rsrc((char *)a.yb + row, keep, W * 64);
-                const rsrc_t rr = row_rsrc((char *)a.rb + (MIDS == 2 ? row : 0), MIDS == 2 && keep, W * 64);
+                unsigned bits = 0;
                 conv_row<MBB, NXT, MID, FIN>(mid[P], off, wt, acc, [&](int pb) {
                     float v[8];
                     relu8(acc[FIN][0][pb], acc[FIN][MBB - 1][pb], bias, v);
-                    if (MIDS == 2) store_row(rr, (int)px0 * 64 + g * 16 + pb * 1024, to_bf16(v));
+                    if (MIDS == 2) bits = mask_push(bits, __builtin_bit_cast(u32x4, to_bf16(v)));
                     const bf16x8 xin = *reinterpret_cast<const bf16x8 *>(&mid[(P + 2) % 3][off[1] + pb * 512]);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) v[q] += (float)xin[q];
                     store_row(ry, (int)px0 * 64 + g * 16 + pb * 1024, to_bf16(v));
                 });
+                if constexpr (MIDS == 2)
+                    store_word(row_rsrc((char *)a.mb + ((int64_t)img * H + o) * W * 4, keep, W * 4), grp * 256 + lane * 4, bits);
             }
-            land(std::integral_constant<int, OUT || MIDS == 2 ? 8 : 4>{}, s);
+            land(std::integral_constant<int, OUT ? 8 : MIDS == 2 ? 5 : 4>{}, s);
         };
         for (int s = 0; s < nsteps; s += 3) {
             step(std::integral_constant<int, 0>{}, s);
@@ -373,20 +320,9 @@ template <int A, bool OUT, int G, int MIDS> hipError_t launch(const SwPairArgs &
         int r = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, k_conv_pair<A, OUT, G, MIDS>, 128 * G, 0) == hipSuccess && r > 0 ? r : 1;
     }();
-    const int64_t slots = (int64_t)sw_device_cus() * resident;
-    int best = a.H, nseg = 1;
-    int64_t best_cost = -1;
-    for (int k = 1; k <= a.H; ++k) {
-        const int rows = (a.H + k - 1) / k, segs = (a.H + rows - 1) / rows;
-        const int64_t cost = ((int64_t)a.B * segs + slots - 1) / slots * (rows + 5);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = rows;
-            nseg = segs;
-        }
-        if (rows <= 4) break;
-    }
-    k_conv_pair<A, OUT, G, MIDS><<<(unsigned)((int64_t)a.B * nseg), 128 * G, 0, s>>>(a, best, nseg);
+    int nseg;
+    const int rows = conv_run_rows(a.B, a.H, (int64_t)sw_device_cus() * resident, 5, &nseg);
+    k_conv_pair<A, OUT, G, MIDS><<<(unsigned)((int64_t)a.B * nseg), 128 * G, 0, s>>>(a, rows, nseg);
     return hipGetLastError();
 }
 
@@ -401,10 +337,9 @@ template <int A, bool OUT, int MIDS> hipError_t launch_w(const SwPairArgs &a, hi
 }
 
 template <int A, bool OUT> hipError_t launch_mids(const SwPairArgs &a, hipStream_t s) {
-    if (!a.ya) return a.ra || a.rb ? hipErrorInvalidValue : launch_w<A, OUT, 0>(a, s);
-    const bool ra = A == RESID, rb = !OUT;                    // the residual blocks of the pair
-    if (!a.ra && !a.rb) return launch_w<A, OUT, 1>(a, s);
-    if ((a.ra != nullptr) != ra || (a.rb != nullptr) != rb) return hipErrorInvalidValue;
+    if (!a.ya) return a.ma || a.mb ? hipErrorInvalidValue : launch_w<A, OUT, 0>(a, s);
+    if (!a.ma && !a.mb) return launch_w<A, OUT, 1>(a, s);
+    if (!a.ma || (a.mb != nullptr) == OUT) return hipErrorInvalidValue;
     return launch_w<A, OUT, 2>(a, s);
 }
 
@@ -416,7 +351,7 @@ hipError_t sw_conv_pair(const SwPairArgs &a, int pair, hipStream_t s) {
     if (a.B < 1 || !sw_conv_pair_fits(a.H, a.W) || (int64_t)a.B * a.H > (int64_t)1 << 30 || !a.wa || !a.wb || !a.ba || !a.bb)
         return hipErrorInvalidValue;
     if (pair == SW_PAIR_OUT ? !a.yf || !a.x : !a.yb) return hipErrorInvalidValue;
-    if (pair == SW_PAIR_FIRST) return a.grids ? (a.ya || a.rb ? hipErrorInvalidValue : launch_w<FIRST_PLANES, false, 0>(a, s))
+    if (pair == SW_PAIR_FIRST) return a.grids ? (a.ya || a.mb ? hipErrorInvalidValue : launch_w<FIRST_PLANES, false, 0>(a, s))
                                              : a.x ? launch_mids<FIRST_DENSE, false>(a, s) : hipErrorInvalidValue;
     if (!a.x) return hipErrorInvalidValue;
     return pair == SW_PAIR_OUT ? launch_mids<RESID, true>(a, s) : launch_mids<RESID, false>(a, s);

@@ -39,8 +39,9 @@ struct sw_net {
     float *wpartial = nullptr;
     SwLayerDesc L[kLayers]{};
     SwLayerDesc *L_dev = nullptr;
-    // NHWC BF16 tensors with halo; relu[k] = relu(Z) of residual block k + 1 (its mask)
-    void *x0 = nullptr, *act[kLayers - 1] = {}, *relu[kLayers - 2] = {}, *g[2] = {}, *dz[2] = {}, *dz6 = nullptr;
+    // NHWC BF16 tensors with halo; mask[l]: where layer l's ReLU is positive, a bit per value (sw_conv_dev.h)
+    void *x0 = nullptr, *act[kLayers - 1] = {}, *g[2] = {}, *dz[3] = {}, *dz6 = nullptr;
+    unsigned *mask[kLayers - 1] = {};
     float *delta = nullptr, *target = nullptr;
     double *dh_part = nullptr;   // rollout: the output layer's per-row sums of dh ([B][H][W / 64])
     double *dh_tile = nullptr;   // fused rollout: per-tile sums of dh ([B][tiles per grid])
@@ -124,7 +125,7 @@ bool use_pairs(const sw_net *n, int B) {
     return n->W <= 128 || (int64_t)B * n->H * n->W >= 200000;
 }
 
-// X0 -> act[0..4] -> delta; with train, also the ReLU parts (backward masks).
+// X0 -> act[0..4] -> delta; with train, also the ReLUs' masks for the backward pass.
 // With `planes` (a rollout) the first layer reads the batch's buffer directly
 // (normalising it and clearing the jump's gate statistics) instead of X0, and
 // the output layer also writes the per-row sums of dh when `dh_part` is set.
@@ -147,10 +148,10 @@ sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const Rollo
             a.ba = n->master + La.b_off;
             a.bb = n->master + Lb.b_off;
             a.ya = planes ? nullptr : n->act[l];
-            if (train && residual(l)) a.ra = n->relu[l - 1];
+            if (train) a.ma = n->mask[l];
             if (l + 1 < kLayers - 1) {
                 a.yb = n->act[l + 1];
-                if (train) a.rb = n->relu[l];
+                if (train) a.mb = n->mask[l + 1];
             } else {
                 a.yf = n->delta;
                 a.yf2 = delta;
@@ -190,10 +191,8 @@ sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const Rollo
             mode = SW_CONV_F32;
         } else {
             a.y = n->act[l];
-            if (residual(l)) {
-                mode = SW_CONV_RESID_BF16;
-                if (train) a.y2 = n->relu[l - 1];
-            }
+            if (residual(l)) mode = SW_CONV_RESID_BF16;
+            if (train) a.mask = n->mask[l];
         }
         SHIP(sw_conv3x3(a, L.cinp, L.cout, mode, s));
     }
@@ -207,24 +206,51 @@ sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const Rollo
 sw_status backward(sw_net *n, int B, float *loss_out, hipStream_t s) {
     SHIP(sw_sur_loss(n->delta, n->target, B, n->H, n->W, n->loss_partial, kLossBlocks, n->dz6, s));
     if (loss_out) SHIP(sw_sur_reduce_sum(n->loss_partial, kLossBlocks, loss_out, s));
-    const void *dz = n->dz6, *gout = nullptr;
-    int dzc = 8;
-    for (int l = kLayers - 1; l >= 0; --l) {
+    auto wgrad = [&](int l, const void *dz) {
         const SwLayerDesc &L = n->L[l];
-        SHIP(sw_sur_wgrad(dz, dzc, L.cout, l == 0 ? n->x0 : n->act[l - 1], L.cinp, L.cin, B, n->H, n->W,
-                          n->wpartial, n->block_cap > 0 ? n->block_cap : kWgradBlocks, n->grad + L.w_off,
-                          n->grad + L.b_off, s));
-        if (l == 0) break;
+        return sw_sur_wgrad(dz, L.coutp, L.cout, l == 0 ? n->x0 : n->act[l - 1], L.cinp, L.cin, B, n->H, n->W, n->wpartial,
+                            n->block_cap > 0 ? n->block_cap : kWgradBlocks, n->grad + L.w_off, n->grad + L.b_off, s);
+    };
+    const bool pairs = use_pairs(n, B);
+    const void *dz = n->dz6, *gout = nullptr;
+    SHIP(wgrad(kLayers - 1, dz));
+    for (int l = kLayers - 1, k = 0; l > 0;) {   // dz of layer l into that of l - 1 (and l - 2); k: dz buffer
+        const SwLayerDesc &L = n->L[l];
+        if (pairs && residual(l)) {              // residual blocks l and l - 1 (the first is l = 1)
+            SwGradPairArgs a{};
+            a.x = dz;
+            a.add = gout;
+            a.wa = L.wd;
+            a.wb = n->L[l - 1].wd;
+            a.ma = n->mask[l - 1];
+            a.mb = n->mask[l - 2];
+            a.za = n->dz[(k + 1) % 3];
+            a.zb = n->dz[(k + 2) % 3];
+            a.yb = l > 2 ? n->g[gout == n->g[0]] : nullptr;
+            a.B = B;
+            a.H = n->H;
+            a.W = n->W;
+            SHIP(sw_grad_pair(a, s));
+            SHIP(wgrad(l - 1, a.za));
+            SHIP(wgrad(l - 2, a.zb));
+            gout = a.yb;
+            dz = a.zb;
+            k = (k + 2) % 3;
+            l -= 2;
+            continue;
+        }
         SwConvArgs a = conv_args(n, B, dz);
         a.w = L.wd;
         a.add = residual(l) ? gout : nullptr;
-        a.mask = l == 1 ? n->act[0] : n->relu[l - 2];
+        a.mask = n->mask[l - 1];
         a.y = residual(l - 1) ? n->g[l & 1] : nullptr;
-        a.y2 = n->dz[l & 1];
+        k = (k + 1) % 3;
+        a.y2 = n->dz[k];
         SHIP(sw_conv3x3(a, L.cdp, L.cin, SW_CONV_DGRAD, s));
+        SHIP(wgrad(l - 1, a.y2));
         gout = a.y;
         dz = a.y2;
-        dzc = 32;
+        l -= 1;
     }
     return SW_OK;
 }
@@ -302,11 +328,9 @@ sw_status sw_surrogate_create(const sw_net_cfg *cfg, int32_t H, int32_t W, int32
     if (st == SW_OK) st = dalloc(n, (void **)&n->L_dev, sizeof(n->L));
     if (st == SW_OK) st = dalloc(n, &n->x0, act_bytes(n, max_batch, 8));
     for (int l = 0; l < kLayers - 1 && st == SW_OK; ++l) st = dalloc(n, &n->act[l], act_bytes(n, max_batch, 32));
-    for (int k = 0; k < kLayers - 2 && st == SW_OK; ++k) st = dalloc(n, &n->relu[k], act_bytes(n, max_batch, 32));
-    for (int k = 0; k < 2 && st == SW_OK; ++k) {
-        st = dalloc(n, &n->g[k], act_bytes(n, max_batch, 32));
-        if (st == SW_OK) st = dalloc(n, &n->dz[k], act_bytes(n, max_batch, 32));
-    }
+    for (int l = 0; l < kLayers - 1 && st == SW_OK; ++l) st = dalloc(n, (void **)&n->mask[l], (size_t)max_batch * H * W * 4);
+    for (int k = 0; k < 2 && st == SW_OK; ++k) st = dalloc(n, &n->g[k], act_bytes(n, max_batch, 32));
+    for (int k = 0; k < 3 && st == SW_OK; ++k) st = dalloc(n, &n->dz[k], act_bytes(n, max_batch, 32));
     if (st == SW_OK) st = dalloc(n, &n->dz6, act_bytes(n, max_batch, 8));
     if (st == SW_OK) st = dalloc(n, (void **)&n->delta, (size_t)max_batch * H * W * 16);
     if (st == SW_OK) st = dalloc(n, (void **)&n->target, (size_t)max_batch * H * W * 16);
