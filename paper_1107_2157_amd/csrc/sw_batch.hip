@@ -158,7 +158,11 @@ __global__ __launch_bounds__(256, (MINW > 0 ? MINW : 1)) void k_batch_step_pers(
 }
 
 // Once per call: ghosts of U^cur for every grid and the max signal speed
-// into ring slot 0.  One wave per tile, lanes across the tile's columns.
+// into ring slot 0.  One wave per part of a tile (blockIdx.y: its rows q, q +
+// parts, ...), lanes across the tile's columns.  A row's loads wait for those
+// of the row before (its ghosts may be stored between them), about 0.6 us a
+// row: a few grids' tiles are dealt to many waves (one grid of 256^2: 19.6
+// us whole, 5.2 in parts of two rows).
 template <typename T>
 __global__ __launch_bounds__(256) void k_batch_prologue(SwBatchLaunch a, int tile_cols) {
     const int tile = batch_tile_index();
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(256) void k_batch_prologue(SwBatchLaunch a, int til
     const int c0 = tt.s * tile_cols, c1 = min(c0 + tile_cols, gd.nx);
     double smax = 0.0;
     bool bad = false;
-    for (int j = j0; j < j1; ++j)
+    for (int j = j0 + blockIdx.y; j < j1; j += gridDim.y)
         for (int i = c0 + lane; i < c1; i += 64) {
             const int64_t off = (int64_t)j * gd.pitch + i;
             U3<T> c = {P[0][off], P[1][off], P[2][off]};
@@ -183,7 +187,7 @@ __global__ __launch_bounds__(256) void k_batch_prologue(SwBatchLaunch a, int til
             if (i == 0 || i == gd.nx - 1 || j == 0 || j == gd.ny - 1)
                 write_ghosts(P, gd.pitch, gd.nx, gd.ny, a.bc_x, a.bc_y, i, j, c);
         }
-    batch_reduce(a, tt.grid, 0, tile, smax, bad);
+    batch_reduce(a, tt.grid, 0, tile + blockIdx.y, smax, bad);
 }
 
 // The masked fallback of the surrogate's rollout in one launch: one
@@ -404,8 +408,10 @@ hipError_t sw_batch_launch_reset(SwBatchScalars *sc, int n, int clear_time, hipS
 
 hipError_t sw_batch_launch_prologue(const SwBatchLaunch &a, int vec, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
-    if (a.dtype) k_batch_prologue<double><<<batch_blocks(a.ntiles), 256, 0, s>>>(a, 64 * vec);
-    else k_batch_prologue<float><<<batch_blocks(a.ntiles), 256, 0, s>>>(a, 64 * vec);
+    // as many parts as bring about 16 waves to a CU, of at least two rows each
+    const dim3 grid(batch_blocks(a.ntiles), (unsigned)std::max(1, std::min(a.rows / 2, 4096 / a.ntiles)));
+    if (a.dtype) k_batch_prologue<double><<<grid, 256, 0, s>>>(a, 64 * vec);
+    else k_batch_prologue<float><<<grid, 256, 0, s>>>(a, 64 * vec);
     return hipGetLastError();
 }
 
