@@ -17,167 +17,159 @@
 // bitwise that of the per-layer path; only the recomputed border costs
 // extra (1.77x the flops at 16 x 16 tiles, 1.54x at 16 x 32).
 //
-// LDS regions are dense, row-major, with their own widths: X (input, 8
-// channels, 16 B per pixel), A (layers 1, 3, 5) and B (layers 2, 4), 32
-// channels (64 B per pixel, its 16-byte chunks swizzled by chunk_off); X and
-// B share one area (X is dead once layer 1 has run), so a 16 x 16 tile needs
-// 80 KB and two workgroups fit on a CU.  Per K step a lane reads one 16-byte
-// chunk; the 64 lanes of a wave read 16 pixels x 64 B.
+// LDS regions are row-major: X (input, 8 channels, 16 B per pixel), A (layers
+// 1, 3, 5) and B (layers 2, 4), 32 channels (64 B per pixel, its 16-byte
+// chunks swizzled by chunk_off), with rows of a multiple of 8 pixels, so that
+// the swizzle, and with it a tap's address, is the same in every row.  X and
+// B share one area (X is dead once layer 1 has run).
+//
+// At the sizes it runs at a CU has one tile, in eight waves that barriers
+// keep in step: what a layer takes is the latency of its operands and the
+// vector instructions around its MFMAs.  Hence a layer's weights stay in
+// registers; the waves take their pixel blocks two at a time, one pair's
+// epilogue among the next one's MFMAs; the weights' rows are dealt to the
+// MFMA's 16-row blocks so that a lane ends with 8 consecutive channels of a
+// pixel, the ones of its operand of the middle tap, which is the residual
+// block's skip; and the barriers wait for LDS alone, not for the next layer's
+// weights.  Measured, the network of one grid of 256^2: 21.8 -> 20.0 us, of
+// which about 13 are its layers' (their MFMAs and, as long, their operands'
+// LDS reads would take 4.6); a rollout of 4 grids (16 x 32 tiles, 64 steps):
+// 575 -> 513 us.  (The weights two K steps ahead and all of a wave's blocks at
+// once before; a layer's weights ahead with the old order of blocks was 5 %
+// slower than that.)
 #include "sw_conv.h"
+#include "sw_conv_dev.h"
 
 #include <algorithm>
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kBorder = 6;   // one pixel per 3x3 layer
-
-// Offset (BF16 elements) of 16-byte chunk c (channels 8c .. 8c + 7) of pixel
-// p in a 32-channel LDS region.  The chunk index is XORed with bits 1-2 of
-// the pixel index: a ds_read_b128 is served 8 lanes (128 bytes, 32 banks) at
-// a time, and those 8 lanes read the same chunk of 8 consecutive pixels,
-// which at a plain 64-byte pixel stride fall on 2 of the 8 bank quads (a
-// 4-way conflict); swizzled they cover all 8.
-__device__ __forceinline__ int chunk_off(int p, int c) { return p * 32 + ((c ^ ((p >> 1) & 3)) << 3); }
 
 template <int TH, int TW> struct Geo {
     static constexpr int h(int l) { return TH + 2 * (kBorder - l); }   // rows of layer l's region (l = 0: input)
     static constexpr int w(int l) { return TW + 2 * (kBorder - l); }
-    static constexpr int X_ELEMS = h(0) * w(0) * 8;
-    static constexpr int A_ELEMS = h(1) * w(1) * 32;
-    static constexpr int B_ELEMS = h(2) * w(2) * 32;
+    static constexpr int s(int l) { return (w(l) + 7) / 8 * 8; }            // its row stride in LDS, pixels
+    static constexpr int X_ELEMS = h(0) * s(0) * 8;
+    static constexpr int A_ELEMS = h(1) * s(1) * 32;
+    static constexpr int B_ELEMS = h(2) * s(2) * 32;
     // X is read only by layer 1 and B first written by layer 2: they share one area
     static constexpr int XB_ELEMS = X_ELEMS > B_ELEMS ? X_ELEMS : B_ELEMS;
 };
 
 // The A operand of M block mb, K step ks of a layer with KS K steps (forward
-// layout: row mb * 16 + n, K elements ks * 32 + 8 g .. + 7).
+// layout: KS * 32 elements a row).  32 output channels: rows dealt so that
+// lane (g, n) ends with channels 8 g + 4 mb .. + 3 of pixel n.
 template <int KS>
-__device__ __forceinline__ bf16x8 load_wk(const __bf16 *Wk, int mb, int ks, int n, int g) {
-    return *reinterpret_cast<const bf16x8 *>(Wk + (int64_t)(mb * 16 + n) * (KS * 32) + ks * 32 + 8 * g);
+__device__ __forceinline__ bf16x8 load_wk(const void *wk, int mb, int ks, int n, int g, bool out) {
+    return *reinterpret_cast<const bf16x8 *>((const __bf16 *)wk + (out ? n : 8 * (n >> 2) + 4 * mb + (n & 3)) * (KS * 32) +
+                                             ks * 32 + 8 * g);
 }
 
-// One layer over its region.  Wave w owns the pixel blocks w, w + NW, ...
-// (NB of them, the last possibly a padding block that stores nothing) and
-// keeps an accumulator per block; the K steps run outermost, so only one K
-// step's weights (the A operands of the M blocks, from the forward layout
-// in global memory: row mb * 16 + n, K elements ks * 32 + 8 g .. + 7) and
-// its B operands are live, and the next step's are loaded while this step's
-// MFMAs run.  Each accumulator still sums its K steps in order, as the
-// per-layer kernel does.  MODE 0: A = relu(Z) (first layer), 1: A = A_prev +
-// relu(Z) (residual blocks), 2: FP32 Z to the prediction (output layer,
-// channels 0..2; returns this lane's sum of channel 0 over the pixels it
-// stored).  (gy0, gx0): grid coordinates of the region's first pixel; bias:
-// the layer's biases in LDS.  wcur holds the weights of K step 0 on entry
-// and, on return, those of the next layer (next_wk), loaded during this
-// layer's last K steps, after which at_last() issues the caller's own loads
-// (the next tile's input), so that no wait for this layer's operands waits
-// for them.
-template <int CIN, int COUT, int MODE, int WOUT, int HOUT, int NW, int MBN, int KSN, typename AtLast>
-__device__ __forceinline__ double run_layer(const __bf16 *src, __bf16 *dst, const void *wk, bf16x8 (&wcur)[2],
-                                            const void *next_wk, const float *bias, int gy0, int gx0, int H, int W,
-                                            float *out, int64_t out_row0, AtLast &&at_last) {
+// One layer over its region.  Wave w owns the 16-pixel blocks w, w + NW, ...
+// (NB of them, the last possibly a padding block that stores nothing), two at
+// a time.  wt: the layer's weights; once the last blocks' MFMAs of K step ks
+// are issued, next(ks) loads what takes their place in the following layer.
+// Each accumulator sums its K steps in order, as the per-layer kernel does.
+// MODE 0: A = relu(Z) (first layer), 1: A = A_prev + relu(Z) (residual
+// blocks), 2: FP32 Z to the prediction (output layer, channels 0..2; returns
+// this lane's sum of channel 0 over the pixels it stored).  WOUT x HOUT: the
+// region; SIN, SOUT: row strides of the source and destination regions.
+// (gy0, gx0): grid coordinates of the region's first pixel; bias: the layer's
+// biases in LDS.  at_last() issues the caller's own loads (the next tile's
+// input) before the last blocks.
+template <int CIN, int COUT, int MODE, int WOUT, int HOUT, int SIN, int SOUT, int NW, typename Next, typename AtLast>
+__device__ __forceinline__ double run_layer(const __bf16 *src, __bf16 *dst, const bf16x8 (&wt)[9][2], Next &&next,
+                                            const float *bias, int gy0, int gx0, int H, int W, float *out,
+                                            int64_t out_row0, AtLast &&at_last) {
     constexpr int KS = CIN == 32 ? 9 : 3;
     constexpr int MB = (COUT + 15) / 16;
     constexpr int NPIX = WOUT * HOUT;
-    constexpr int NBLK = (NPIX + 15) / 16;
-    constexpr int NB = (NBLK + NW - 1) / NW;     // blocks per wave
-    constexpr int WIN = WOUT + 2;                // source region width
+    constexpr int NB = ((NPIX + 15) / 16 + NW - 1) / NW;     // blocks per wave
+    static_assert(CIN == 8 || SIN % 8 == 0, "a tap's swizzle must not depend on the row");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
-    const __bf16 *Wk = (const __bf16 *)wk;
-    int sb[NB], pp[NB];
+    float bl[8];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const int p = (wave + k * NW) * 16 + n;
-        pp[k] = p;
-        const int pc = p < NPIX ? p : NPIX - 1;  // padding lanes and blocks read a real pixel, store nothing
-        const int r = pc / WOUT;
-        sb[k] = r * WIN + (pc - r * WOUT);
-    }
-    auto load_w = [&](int ks, bf16x8 (&wa)[MB]) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) wa[mb] = load_wk<KS>(Wk, mb, ks, n, g);
-    };
-    auto load_b = [&](int ks, bf16x8 (&xb)[NB]) {
-        const int tap = CIN == 32 ? ks : 4 * ks + g;
-        const bool live = tap < 9;
-        const int off = live ? (tap / 3) * WIN + tap % 3 : 0;
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            if (CIN == 32)
-                xb[k] = *reinterpret_cast<const bf16x8 *>(src + chunk_off(sb[k] + off, g));
-            else
-                xb[k] = *reinterpret_cast<const bf16x8 *>(src + (sb[k] + off) * 8);
-            if (!live) xb[k] = bf16x8{};
-        }
-    };
-    f32x4 acc[MB][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int k = 0; k < NB; ++k) acc[mb][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // weights run WD K steps ahead (a global load's latency is longer than one
-    // K step's MFMAs), B operands one step ahead
-    constexpr int WD = KS > 2 ? 2 : 1;
-    bf16x8 wa[WD + 1][MB], xb[2][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) wa[0][mb] = wcur[mb];
-#pragma unroll
-    for (int d = 1; d < WD; ++d) load_w(d, wa[d]);
-    load_b(0, xb[0]);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        if (ks + WD < KS) load_w(ks + WD, wa[(ks + WD) % (WD + 1)]);
-        if (ks + WD == KS) {   // the next layer's first weights (MBN M blocks, KSN K steps)
-#pragma unroll
-            for (int mb = 0; mb < MBN; ++mb) wcur[mb] = load_wk<KSN>((const __bf16 *)next_wk, mb, 0, n, g);
-        }
-        if (ks + 1 < KS) load_b(ks + 1, xb[(ks + 1) & 1]);
-        else at_last();        // then what the caller issues last
-#pragma unroll
-        for (int k = 0; k < NB; ++k)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                acc[mb][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[ks % (WD + 1)][mb], xb[ks & 1][k], acc[mb][k],
-                                                                     0, 0, 0);
-    }
-    // epilogue: lane holds channels mb * 16 + 4 g .. + 3 of pixel pp[k]
+    for (int q = 0; q < 8; ++q) bl[q] = bias[MODE == 2 ? q & 3 : 8 * g + q];
     double dh = 0.0;
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        if (pp[k] >= NPIX) continue;
-        const int r = pp[k] / WOUT, c = pp[k] - (pp[k] / WOUT) * WOUT;
-        const int gy = gy0 + r, gx = gx0 + c;
+    struct Block {
+        f32x4 acc[MB];
+        bf16x8 skip;
+        int p, r, c;
+    };
+    auto finish = [&](const Block &v) {
+        if (v.p >= NPIX) return;
+        const int gy = gy0 + v.r, gx = gx0 + v.c;
         if constexpr (MODE == 2) {
-            if (g != 0 || gy >= H) continue;                    // lanes of group 0 hold channels 0..3
-            f32x4 v = acc[0][k];
+            if (g != 0 || gy >= H) return;                   // lanes of group 0 hold channels 0..3
+            f32x4 o = v.acc[0];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = q < COUT ? v[q] + bias[q] : 0.f;
-            *reinterpret_cast<f32x4 *>(out + (out_row0 + (int64_t)r * W + c) * 4) = v;
-            dh += (double)v[0];
+            for (int q = 0; q < 4; ++q) o[q] = q < COUT ? o[q] + bl[q] : 0.f;
+            *reinterpret_cast<f32x4 *>(out + (out_row0 + (int64_t)v.r * W + v.c) * 4) = o;
+            dh += (double)o[0];
         } else {
             const bool inside = gy >= 0 && gy < H && gx >= 0 && gx < W;
+            float f[8];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                f32x4 v = acc[mb][k];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q] + bias[mb * 16 + 4 * g + q], 0.f);
-                if (MODE == 1) {
-                    const bf16x4 xin = *reinterpret_cast<const bf16x4 *>(
-                        src + chunk_off(sb[k] + WIN + 1, 2 * mb + (g >> 1)) + 4 * (g & 1));
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] += (float)xin[q];
-                }
-                bf16x4 o = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                if (!inside) o = bf16x4{};
-                *reinterpret_cast<bf16x4 *>(dst + chunk_off(pp[k], 2 * mb + (g >> 1)) + 4 * (g & 1)) = o;
+            for (int q = 0; q < 8; ++q) {
+                f[q] = fmaxf(v.acc[q >> 2][q & 3] + bl[q], 0.f);
+                if (MODE == 1) f[q] += (float)v.skip[q];
             }
+            u32x4 o = __builtin_bit_cast(u32x4, to_bf16(f));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = inside ? o[q] : 0u;
+            *reinterpret_cast<u32x4 *>(dst + chunk_off(v.r * SOUT + v.c, g)) = o;
+        }
+    };
+    Block blk[2][2];                                         // the pair at hand and the one before
+#pragma unroll
+    for (int k = 0; k < NB; k += 2) {
+        Block(&cur)[2] = blk[(k >> 1) & 1];
+        const int m = k + 1 < NB ? 2 : 1;
+        const bool last = k + 2 >= NB;
+        if (last) at_last();
+        const __bf16 *at[2][3];
+#pragma unroll
+        for (int i = 0; i < m; ++i) {
+            cur[i].p = (wave + (k + i) * NW) * 16 + n;
+            const int pc = min(cur[i].p, NPIX - 1);          // padding lanes read a real pixel, store nothing
+            cur[i].r = pc / WOUT;
+            cur[i].c = pc - cur[i].r * WOUT;
+            const int sb = cur[i].r * SIN + cur[i].c;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                if (CIN == 32) {
+                    at[i][d] = src + chunk_off(sb + d, g);   // column tap d of row tap 0
+                } else {                                     // K step d: tap 4 d + g
+                    const int tap = min(4 * d + g, 8);
+                    at[i][d] = src + (sb + tap / 3 * SIN + tap % 3) * 8;
+                }
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) cur[i].acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 x[2];
+#pragma unroll
+            for (int i = 0; i < m; ++i) {
+                x[i] = *reinterpret_cast<const bf16x8 *>(CIN == 32 ? at[i][ks % 3] + ks / 3 * (SIN * 32) : at[i][ks]);
+                if (CIN == 8 && ks == 2 && g != 0) x[i] = bf16x8{};   // taps 9 .. 11 do not exist
+                if (MODE == 1 && ks == 4) cur[i].skip = x[i];
+            }
+#pragma unroll
+            for (int i = 0; i < m; ++i)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) cur[i].acc[mb] = mfma(wt[ks][mb], x[i], cur[i].acc[mb]);
+            if (last) next(ks);
+            if (ks == KS / 3 && k > 0)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) finish(blk[((k >> 1) & 1) ^ 1][i]);
         }
     }
+#pragma unroll
+    for (int i = 0; i < (NB % 2 ? 1 : 2); ++i) finish(blk[((NB - 1) >> 1) & 1][i]);
     return dh;
 }
 
@@ -238,15 +230,29 @@ __global__ __launch_bounds__(64 * NW) void k_net_fused(SwNetFusedArgs a, int til
                            (__bf16)((rp[j] - a.nrm.in_off[1]) / a.nrm.in_scale[1]),
                            (__bf16)((rq[j] - a.nrm.in_off[2]) / a.nrm.in_scale[2]),
                            (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
-            *reinterpret_cast<bf16x8 *>(sx + i * 8) = v;
+            const int r = i / G::w(0);
+            *reinterpret_cast<bf16x8 *>(sx + (r * G::s(0) + i - r * G::w(0)) * 8) = v;
         }
     };
     auto nothing = [] {};
     const int lane16 = lane & 15, g4 = lane >> 4;
-    bf16x8 wcur[2];
+    // weights of the layer that runs; the first layer has only 3 K steps, the rest of the second's are loaded before it
+    bf16x8 wt[9][2];
+    auto load_first = [&](int ks) {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) wcur[mb] = load_wk<3>((const __bf16 *)a.wk[0], mb, 0, lane16, g4);
+        for (int mb = 0; mb < 2; ++mb)
+            if (ks < 3) wt[ks][mb] = load_wk<3>(a.wk[0], mb, ks, lane16, g4, false);
+    };
+    auto load_of = [&](int l) {                               // layer l's (1 .. 5)
+        return [&, l](int ks) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+                if (l < 5 || mb == 0) wt[ks][mb] = load_wk<9>(a.wk[l], mb, ks, lane16, g4, l == 5);
+        };
+    };
     if (blockIdx.x < ntiles) stage_load(blockIdx.x);
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) load_first(ks);
 
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {   // uniform per block
         const int b = t / (tiles_y * tiles_x);
@@ -261,24 +267,26 @@ __global__ __launch_bounds__(64 * NW) void k_net_fused(SwNetFusedArgs a, int til
             st.nonfinite = 0u;
         }
         stage_store();
-        __syncthreads();
-        run_layer<8, 32, 0, G::w(1), G::h(1), NW, 2, 9>(sx, sa, a.wk[0], wcur, a.wk[1], s_bias[0], y0 - 5, x0 - 5, H,
+        lds_barrier();
+#pragma unroll
+        for (int ks = 3; ks < 9; ++ks) load_of(1)(ks);
+        run_layer<8, 32, 0, G::w(1), G::h(1), G::s(0), G::s(1), NW>(sx, sa, wt, load_of(1), s_bias[0], y0 - 5, x0 - 5, H,
                                                         W, nullptr, 0, nothing);
-        __syncthreads();
-        run_layer<32, 32, 1, G::w(2), G::h(2), NW, 2, 9>(sa, sbf, a.wk[1], wcur, a.wk[2], s_bias[1], y0 - 4, x0 - 4,
+        lds_barrier();
+        run_layer<32, 32, 1, G::w(2), G::h(2), G::s(1), G::s(2), NW>(sa, sbf, wt, load_of(2), s_bias[1], y0 - 4, x0 - 4,
                                                          H, W, nullptr, 0, nothing);
-        __syncthreads();
-        run_layer<32, 32, 1, G::w(3), G::h(3), NW, 2, 9>(sbf, sa, a.wk[2], wcur, a.wk[3], s_bias[2], y0 - 3, x0 - 3,
+        lds_barrier();
+        run_layer<32, 32, 1, G::w(3), G::h(3), G::s(2), G::s(3), NW>(sbf, sa, wt, load_of(3), s_bias[2], y0 - 3, x0 - 3,
                                                          H, W, nullptr, 0, nothing);
-        __syncthreads();
-        run_layer<32, 32, 1, G::w(4), G::h(4), NW, 2, 9>(sa, sbf, a.wk[3], wcur, a.wk[4], s_bias[3], y0 - 2, x0 - 2,
+        lds_barrier();
+        run_layer<32, 32, 1, G::w(4), G::h(4), G::s(3), G::s(4), NW>(sa, sbf, wt, load_of(4), s_bias[3], y0 - 2, x0 - 2,
                                                          H, W, nullptr, 0, nothing);
-        __syncthreads();
-        run_layer<32, 32, 1, G::w(5), G::h(5), NW, 1, 9>(sbf, sa, a.wk[4], wcur, a.wk[5], s_bias[4], y0 - 1, x0 - 1,
+        lds_barrier();
+        run_layer<32, 32, 1, G::w(5), G::h(5), G::s(4), G::s(5), NW>(sbf, sa, wt, load_of(5), s_bias[4], y0 - 1, x0 - 1,
                                                          H, W, nullptr, 0, nothing);
-        __syncthreads();
+        lds_barrier();
         const int tn = t + gridDim.x;
-        double dh = run_layer<32, 3, 2, TW, TH, NW, 2, 3>(sa, nullptr, a.wk[5], wcur, a.wk[0], s_bias[5], y0, x0, H, W,
+        double dh = run_layer<32, 3, 2, TW, TH, G::s(5), TW, NW>(sa, nullptr, wt, load_first, s_bias[5], y0, x0, H, W,
                                                           a.delta, ((int64_t)b * H + y0) * W + x0, [&] {
                                                               if (tn < ntiles) stage_load(tn);
                                                           });
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(64 * NW) void k_net_fused(SwNetFusedArgs a, int til
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) dh += __shfl_xor(dh, o);
         if (lane == 0) s_dh[wave] = dh;
-        __syncthreads();                                     // also: the next tile's staging may overwrite sx / sa
+        lds_barrier();                                       // also: the next tile's staging may overwrite sx / sa
         if (threadIdx.x == 0 && a.dh_tile) {
             double s = 0.0;
             for (int k = 0; k < NW; ++k) s += s_dh[k];
