@@ -114,11 +114,13 @@ __global__ __launch_bounds__(128 * G, 2) void k_grad_pair(SwGradPairArgs a, int 
             });
             lds_barrier();
         };
-        for (int s = 0; s < nsteps; s += 3) {
+        // (what the last step would compute, nobody reads)
+        for (int s = 0; s < nsteps - 1; s += 3) {
             step(std::integral_constant<int, 0>{}, s);
-            if (s + 1 < nsteps) step(std::integral_constant<int, 1>{}, s + 1);
-            if (s + 2 < nsteps) step(std::integral_constant<int, 2>{}, s + 2);
+            if (s + 1 < nsteps - 1) step(std::integral_constant<int, 1>{}, s + 1);
+            if (s + 2 < nsteps - 1) step(std::integral_constant<int, 2>{}, s + 2);
         }
+        lds_barrier();
         return;
     }
     // ---- role b: reads row ys - 4 + s of za, finishes row o = ys - 5 + s
@@ -149,6 +151,15 @@ __global__ __launch_bounds__(128 * G, 2) void k_grad_pair(SwGradPairArgs a, int 
             lds_dma16(kind[k] == 0 ? xr : kind[k] == 1 ? mra : mrb, soff[k],
                       ldst[k] + slot * (unsigned)(kind[k] ? sizeof(mask[0]) : sizeof(in[0])));
     };
+    // End of step s: step s + 1's row and masks are in.  They were issued at the start of step s + 1 - kAhead; newer are
+    // those issued since and the stores of kAhead steps (ST a step from step 3 on; vector memory operations end in
+    // order).  The first were waited for before the first step; rows past the last are issued all the same.
+    auto land = [&](auto st, int s) {
+        constexpr int ST = decltype(st)::value;
+        if (s >= kAhead + 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kAhead - 1) * PERW + kAhead * ST) : "memory");
+        else if (s >= kAhead - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kAhead - 1) * PERW) : "memory");
+        lds_barrier();
+    };
     for (int s = 0; s < kAhead; ++s) issue(s);
     wait_vm_upto<0>(0);
     lds_barrier();
@@ -173,14 +184,14 @@ __global__ __launch_bounds__(128 * G, 2) void k_grad_pair(SwGradPairArgs a, int 
             if (GB) store_row(ry, px0 * 64 + g * 16 + pb * 1024, gb);
             store_row(rz, px0 * 64 + g * 16 + pb * 1024, mask_keep(gb, m, pb));
         });
-        // step s + 1's row and masks are in: they were issued at the start of step s + 1 - kAhead; newer are those
-        // issued since and the stores of kAhead steps (vector memory operations end in order).  The first were waited
-        // for before the first step; rows past the last are issued all the same.
-        if (s >= kAhead - 1)
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kAhead - 1) * PERW + kAhead * (GB ? 8 : 4)) : "memory");
-        lds_barrier();
+        land(std::integral_constant<int, GB ? 8 : 4>{}, s);
     };
-    for (int s = 0; s < nsteps; s += 3) {
+    // (role a's first row of use is there in step 3)
+    for (int s = 0; s < 3; ++s) {
+        issue(s + kAhead);
+        land(std::integral_constant<int, 0>{}, s);
+    }
+    for (int s = 3; s < nsteps; s += 3) {
         step(std::integral_constant<int, 0>{}, s);
         if (s + 1 < nsteps) step(std::integral_constant<int, 1>{}, s + 1);
         if (s + 2 < nsteps) step(std::integral_constant<int, 2>{}, s + 2);

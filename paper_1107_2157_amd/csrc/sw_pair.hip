@@ -137,11 +137,14 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
     for (int dx = 0; dx < 3; ++dx) off[dx] = chunk_off(grp * 64 + n + dx, g);
     const int64_t px0 = grp * 64 + n;
     // End of step s: row s + 1 is in.  It was issued at the start of step s + 1 - AHEAD; newer are the rows issued
-    // since and the stores of AHEAD steps (ST of them a step, dropped ones too; vector memory operations end in order).
-    // The first rows were waited for before the first step; rows past the last are issued all the same.
-    auto land = [&](auto st, int s) {
+    // since and the stores of AHEAD steps (ST of them a step from step `first` on, dropped ones too; vector memory
+    // operations end in order).  The first rows were waited for before the first step; rows past the last are issued
+    // all the same.
+    auto land = [&](auto st, int s, int first) {
         if constexpr (A != FIRST_PLANES) {
-            if (s >= AHEAD - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * PERW + AHEAD * decltype(st)::value) : "memory");
+            constexpr int ST = decltype(st)::value;
+            if (s >= first + AHEAD - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * PERW + AHEAD * ST) : "memory");
+            else if (s >= AHEAD - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * PERW) : "memory");
         }
         lds_barrier();
     };
@@ -233,13 +236,15 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
             if constexpr (MIDS == 2)
                 store_word(row_rsrc((char *)a.ma + ((int64_t)img * H + r) * W * 4, keep, W * 4), grp * 256 + lane * 4, bits);
             store_planes(s + AHEAD);
-            land(std::integral_constant<int, MIDS == 0 ? 0 : MIDS == 2 ? 5 : 4>{}, s);
+            land(std::integral_constant<int, MIDS == 0 ? 0 : MIDS == 2 ? 5 : 4>{}, s, 0);
         };
-        for (int s = 0; s < nsteps; s += 3) {
+        // (what the last step would compute, nobody reads)
+        for (int s = 0; s < nsteps - 1; s += 3) {
             step(std::integral_constant<int, 0>{}, s);
-            if (s + 1 < nsteps) step(std::integral_constant<int, 1>{}, s + 1);
-            if (s + 2 < nsteps) step(std::integral_constant<int, 2>{}, s + 2);
+            if (s + 1 < nsteps - 1) step(std::integral_constant<int, 1>{}, s + 1);
+            if (s + 2 < nsteps - 1) step(std::integral_constant<int, 2>{}, s + 2);
         }
+        lds_barrier();
     } else {
         // ---- role b
         bf16x8 wt[9][MBB];
@@ -302,9 +307,14 @@ __global__ __launch_bounds__(128 * G, 2) void k_conv_pair(SwPairArgs a, int rows
                 if constexpr (MIDS == 2)
                     store_word(row_rsrc((char *)a.mb + ((int64_t)img * H + o) * W * 4, keep, W * 4), grp * 256 + lane * 4, bits);
             }
-            land(std::integral_constant<int, OUT ? 8 : MIDS == 2 ? 5 : 4>{}, s);
+            land(std::integral_constant<int, OUT ? 8 : MIDS == 2 ? 5 : 4>{}, s, 3);
         };
-        for (int s = 0; s < nsteps; s += 3) {
+        // (role a's first row of use is there in step 3)
+        for (int s = 0; s < 3; ++s) {
+            issue(s + AHEAD);
+            land(std::integral_constant<int, 0>{}, s, 3);
+        }
+        for (int s = 3; s < nsteps; s += 3) {
             step(std::integral_constant<int, 0>{}, s);
             if (s + 1 < nsteps) step(std::integral_constant<int, 1>{}, s + 1);
             if (s + 2 < nsteps) step(std::integral_constant<int, 2>{}, s + 2);

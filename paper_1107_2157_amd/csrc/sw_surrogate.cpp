@@ -495,10 +495,10 @@ namespace {
 // automatic mode: while the batch has at most kFusedMaxTiles 16 x 32 output
 // tiles per CU.  The fused launch recomputes a 6-pixel border of every tile
 // (1.5-1.8x the flops) but moves only the state and the prediction through
-// HBM and takes one launch per jump instead of six; measured on MI355X with
-// 256^2 grids (128 such tiles each), the whole 64-step rollout is 1.37x
-// faster than with per-layer launches at batch 1, 1.05x at batch 4 (2 tiles
-// per CU), and 0.94x at batch 8.
+// HBM and takes one launch per jump instead of three or six; measured on
+// MI355X with 256^2 grids (128 such tiles each), the 64-step rollout fused
+// and not: batch 1 246 / 445 us, 2 389 / 490, 4 (2 tiles per CU) 515 / 623, 5
+// 685 / 666, 8 864 / 795.
 constexpr int kFusedMaxTiles = 2;
 bool rollout_fused(const sw_net *n, int B) {
     if (n->fused_mode != 2) return n->fused_mode == 1;
