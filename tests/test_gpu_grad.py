@@ -1,7 +1,7 @@
 """The backward pass where its kernels' runs of rows begin, end and cross from
-one image to the next, at one to five column groups: every entry of the
-gradient against the oracle's backward pass fed the GPU's forward pass, within
-the bound of the same comparison in test_gpu_surrogate.py."""
+one image to the next, and where batches go row by row or tile by tile: every
+entry of the gradient against the oracle's backward pass fed the GPU's forward
+pass, within the bound of the same comparison in test_gpu_surrogate.py."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,H,W,cap", [(1, 3, 64, 0), (5, 1, 64, 2), (3, 7, 128, 0), (2, 13, 192, 0), (1, 300, 192, 0),
-                                       (2, 5, 256, 0), (4, 200, 256, 0), (3, 11, 320, 5), (2, 9, 512, 0)])
+                                       (2, 5, 256, 0), (4, 200, 256, 0), (3, 11, 320, 5), (2, 9, 512, 0),
+                                       (10, 241, 256, 0), (10, 241, 256, 7), (60, 20, 512, 0)])
 def test_gradient_at_run_edges(B, H, W, cap):
     p, out_scale, u, u8 = grad_case(B, H, W, 16)
     announce(f"surrogate gradient at run edges B={B} {H}x{W} cap={cap}")
