@@ -422,9 +422,10 @@ sw_status sw_surrogate_advance(sw_net *net, sw_batch *solver, int32_t nsteps, co
  * Results are identical either way.  Errors: SW_EINVAL for a NULL network. */
 sw_status sw_surrogate_set_graph(sw_net *net, int32_t enable);
 /* Upper bound on the workgroups of the persistent convolution and
- * weight-gradient kernels (each walks a contiguous run of tiles); 0 (the
- * default) launches one workgroup per slot the device holds at once.  A
- * smaller cap only changes how the tiles are split among workgroups: the
+ * weight-gradient kernels (each walks a contiguous run of tiles or rows); 0
+ * (the default) launches one workgroup per slot the device holds at once, and
+ * takes the layers two per launch where that is faster (a cap, one per
+ * launch).  A cap only changes how the work is split among workgroups: the
  * convolution outputs are bitwise unchanged, the weight gradient's FP32 block
  * partials (summed in FP64) split differently.  Drops captured rollouts.
  * Errors: SW_EINVAL for a NULL network or a cap outside [0, 1024]. */
@@ -433,12 +434,13 @@ sw_status sw_surrogate_set_block_cap(sw_net *net, int32_t max_blocks);
 /* Form of the rollout's network pass.  1: one launch runs all six layers
  * per output tile with the activations on chip (the state with a 6-pixel
  * border in, the prediction out), and the gate's verdict and the rejected
- * grids' solver steps share one launch: three launches per jump.  0: one
- * launch per layer through activation tensors in device memory, then
- * separate gate and fallback launches.  2 (default): 1 while the batch has
- * at most 2 output tiles of 16 x 32 pixels per compute unit, else 0 (the
- * fused form recomputes each tile's border and wins where launches and HBM
- * traffic dominate, i.e. at small batches).  The predictions are bitwise
+ * grids' solver steps share one launch: three launches per jump.  0: the
+ * layers through activation tensors in device memory, two per launch where
+ * the grids are up to 256 wide and not a few small ones of 192 or 256 (or
+ * one per launch), then separate gate and fallback launches.  2 (default):
+ * 1 while the batch has at most 2 output tiles of 16 x 32 pixels per compute
+ * unit, else 0 (the fused form recomputes each tile's border and wins where
+ * launches and HBM traffic dominate, i.e. at small batches).  The predictions are bitwise
  * equal; with project_mass the mean of the predicted dh is summed in a
  * different fixed order (per tile instead of per row segment), so h may
  * differ in the last bits.  Drops captured rollouts.

@@ -509,8 +509,8 @@ class Surrogate:
         check(lib().sw_surrogate_set_block_cap(self.handle, max_blocks), "sw_surrogate_set_block_cap")
 
     def set_fused(self, mode):
-        """Rollout network form: 1 / True one fused launch per jump, 0 / False one launch
-        per layer, 2 (the default) whichever the batch size favours."""
+        """Rollout network form: 1 / True one fused launch per jump, 0 / False the
+        layers one or two per launch, 2 (the default) whichever the batch size favours."""
         check(lib().sw_surrogate_set_fused(self.handle, int(mode)), "sw_surrogate_set_fused")
 
     def forward(self, u: torch.Tensor) -> torch.Tensor:

@@ -50,6 +50,36 @@ def test_equals_per_step_launches(nx, ny, dtype, scheme):
             same(a, b, f"{steps} steps, bc {bc_x}{bc_y}")
 
 
+@pytest.mark.parametrize("scheme", [sw.SCHEME_PAPER, sw.SCHEME_TRANSVERSE])
+@pytest.mark.parametrize("how", [dict(dx=0.3, dy=0.7), dict(dx=3.0, dy=0.11, cfl=0.4), dict(dx=0.3, dy=0.7, cfl=0.0, dt_fixed=1e-3)])
+def test_spacings_and_fixed_dt(how, scheme):
+    announce(f"resident spacings {how} scheme={scheme}")
+    for dtype in ("f32", "f64"):
+        a, b = pair(190, 70, dtype=dtype, bc_y=sw.PERIODIC, scheme=scheme, **how)
+        u = ics.random_state(190, 70, seed=5)
+        a.set_state(*u)
+        b.set_state(*u)
+        for steps in (1, 8):
+            a.step(steps)
+            b.step(steps)
+            same(a, b, f"{dtype} {steps} steps")
+
+
+def test_unstable_state():
+    """A dry cell: both report it, and end with the same bits, NaN included."""
+    announce("resident unstable 130x70 f32")
+    a, b = pair(130, 70, dtype="f32")
+    u = [x.clone() if torch.is_tensor(x) else x.copy() for x in ics.random_state(130, 70, seed=6)]
+    u[0][30, 64] = -1.0
+    for s in (a, b):
+        s.set_state(*u)
+        s.step(6)
+        with pytest.raises(sw.Unstable):
+            s.sync_status()
+    for x, y in zip(a.get_state(halo=True), b.get_state(halo=True)):
+        assert torch.equal(x.contiguous().view(torch.int32), y.contiguous().view(torch.int32))
+
+
 BATCHES = [([(64, 64), (192, 192), (130, 130), (320, 320), (5, 40), (1, 1)], "f32"),
            ([(256, 256)] * 70, "f32"), ([(48, 100), (300, 33), (700, 260)], "f64"),
            ([(512, 512)] * 30, "f32")]
