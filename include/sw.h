@@ -390,9 +390,11 @@ sw_status sw_surrogate_set_norm(sw_net *net, const float in_offset[3], const flo
 sw_status sw_surrogate_forward(sw_net *net, const float *u, int32_t B, float *delta, void *stream);
 /* Device pointer to the last forward pass's activations: layer 0 = network
  * input (BF16 NHWC, 8 channels, with halo), 1..5 = hidden layers (BF16 NHWC,
- * 32 channels, with halo), 6 = delta (FP32 [B][H][W][4]).  A rollout's
- * first layer reads the batch's planes directly and leaves layer 0 as the
- * last sw_surrogate_forward / grad / train_step wrote it. */
+ * 32 channels, with halo), 6 = delta (FP32 [B][H][W][4]).  A rollout by
+ * layers shows its last jump's, but its first layer reads the batch's planes
+ * directly and leaves layer 0 as the last sw_surrogate_forward / grad /
+ * train_step wrote it; a fused rollout (sw_surrogate_set_fused) writes layer 6
+ * alone. */
 sw_status sw_surrogate_activation(sw_net *net, int32_t layer, const void **ptr, int64_t *bytes);
 /* Async.  Loss (device float, may be NULL) and gradient (device, nparams
  * floats, may be NULL) of the pair (u -> u8), without updating. */

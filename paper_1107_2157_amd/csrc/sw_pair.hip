@@ -361,8 +361,11 @@ hipError_t sw_conv_pair(const SwPairArgs &a, int pair, hipStream_t s) {
     if (a.B < 1 || !sw_conv_pair_fits(a.H, a.W) || (int64_t)a.B * a.H > (int64_t)1 << 30 || !a.wa || !a.wb || !a.ba || !a.bb)
         return hipErrorInvalidValue;
     if (pair == SW_PAIR_OUT ? !a.yf || !a.x : !a.yb) return hipErrorInvalidValue;
-    if (pair == SW_PAIR_FIRST) return a.grids ? (a.ya || a.mb ? hipErrorInvalidValue : launch_w<FIRST_PLANES, false, 0>(a, s))
-                                             : a.x ? launch_mids<FIRST_DENSE, false>(a, s) : hipErrorInvalidValue;
+    if (pair == SW_PAIR_FIRST && a.grids) {
+        if (a.ma || a.mb) return hipErrorInvalidValue;
+        return a.ya ? launch_w<FIRST_PLANES, false, 1>(a, s) : launch_w<FIRST_PLANES, false, 0>(a, s);
+    }
+    if (pair == SW_PAIR_FIRST) return a.x ? launch_mids<FIRST_DENSE, false>(a, s) : hipErrorInvalidValue;
     if (!a.x) return hipErrorInvalidValue;
     return pair == SW_PAIR_OUT ? launch_mids<RESID, true>(a, s) : launch_mids<RESID, false>(a, s);
 }

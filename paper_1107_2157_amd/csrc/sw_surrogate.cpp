@@ -133,9 +133,11 @@ struct RolloutInput {
     const SwBatchGrid *grids;
     int cur;
     bool dh_sums;
+    bool last;   // the call's last network pass: its activations are the ones sw_surrogate_activation shows
 };
 // delta (optional): a second copy of the prediction.  With two layers a
-// launch (use_pairs) a rollout leaves the activations between them unwritten.
+// launch (use_pairs) the activations between them are written where somebody
+// can see them: not in a rollout's jumps before its last.
 sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const RolloutInput *planes = nullptr,
                   float *delta = nullptr) {
     if (use_pairs(n, B)) {
@@ -147,7 +149,7 @@ sw_status forward(const sw_net *n, int B, bool train, hipStream_t s, const Rollo
             a.wb = Lb.wk;
             a.ba = n->master + La.b_off;
             a.bb = n->master + Lb.b_off;
-            a.ya = planes ? nullptr : n->act[l];
+            a.ya = planes && !planes->last ? nullptr : n->act[l];
             if (train) a.ma = n->mask[l];
             if (l + 1 < kLayers - 1) {
                 a.yb = n->act[l + 1];
@@ -513,7 +515,8 @@ sw_status enqueue_rollout(sw_net *n, sw_batch *solver, const SwBatchInfo &bi, in
     sw_status st;
     if ((st = sw_batch_fill_halo(solver, s)) != SW_OK) return st;
     const bool fused = rollout_fused(n, B);
-    for (int j = 0; j < nsteps / n->cfg.jump; ++j) {
+    const int njumps = nsteps / n->cfg.jump;
+    for (int j = 0; j < njumps; ++j) {
         if (fused) {
             // the network in one launch, the update with the gate's statistics, then the gate's verdict and
             // the rejected grids' solver steps in one launch
@@ -545,7 +548,7 @@ sw_status enqueue_rollout(sw_net *n, sw_batch *solver, const SwBatchInfo &bi, in
             continue;
         }
         // U^n in buffer cur; every grid's U^{n+jump} ends in buffer cur ^ 1
-        const RolloutInput in{bi.d_grids, cur, gate->project_mass != 0};
+        const RolloutInput in{bi.d_grids, cur, gate->project_mass != 0, j + 1 == njumps};
         if ((st = forward(n, B, false, s, &in)) != SW_OK) return st;
         SHIP(sw_sur_apply(n->delta, n->dh_part, n->H * (n->W / 64), bi.d_grids, cur, B, n->H, n->W, n->nrm,
                           gate->project_mass, bi.bc_x, bi.bc_y, n->stats, n->apply_part, n->apply_ticket, s));
