@@ -3,9 +3,10 @@
 //
 // The workgroups of a team wait for each other, so all of them have to be
 // resident at once.  Two things see to that.  (1) A grid is cut into at most
-// one workgroup per compute unit, and a launch is held back (by an event
-// wait on its stream) until the resident launches before it that this
-// process still has in flight leave it that many compute units.  Other
+// one workgroup per compute unit, and a launch is ordered (by event waits on
+// its stream) behind the resident launches of this process whose compute
+// units it takes over (sw_admission.h), so that those that can run at the same
+// time have room together.  Other
 // kernels on the device only delay a team: they end by themselves.  A batch
 // launches more workgroups than fit: workgroups start in order of their
 // index (on each XCD), so the teams of the lowest indices are complete first
@@ -16,11 +17,12 @@
 
 #include <algorithm>
 #include <cmath>
-#include <deque>
+#include <map>
 #include <mutex>
 #include <numeric>
 #include <vector>
 
+#include "sw_admission.h"
 #include "sw_resident.h"
 
 bool sw_res_cut(int dtype, int nx, int ny, int64_t pitch, int nw, int max_rows, int max_wg, bool spread, SwResPlan *out) {
@@ -187,21 +189,13 @@ hipError_t sw_res_launch(const SwResArgs &a, int dtype, int scheme, int rows, bo
 
 namespace {
 
-// The resident launches in flight on each device: compute units each may
-// hold, and an event recorded behind it.  At most kInFlight are kept; they
-// are dropped when done, or when a later launch has been ordered behind them.
-constexpr size_t kInFlight = 16;
-struct Flight {
-    hipEvent_t done;
-    int cus;
-};
 struct Device {
-    std::deque<Flight> flights;
+    SwCuPool<hipStream_t, hipEvent_t> pool;
     std::vector<hipEvent_t> spare;
 };
 std::mutex g_mutex;
-std::vector<Device> &devices() {
-    static auto *d = new std::vector<Device>();   // never destroyed: the HIP runtime may go first at exit
+std::map<int, Device> &devices() {
+    static auto *d = new std::map<int, Device>();   // never destroyed: the HIP runtime may go first at exit
     return *d;
 }
 
@@ -210,39 +204,45 @@ std::vector<Device> &devices() {
 hipError_t sw_res_launch_admitted(const SwResArgs &a, int dtype, int scheme, int rows, bool exact, int nw, int nwg,
                                   int device, int cus, hipStream_t s) {
     std::lock_guard<std::mutex> hold(g_mutex);
-    auto &all = devices();
-    if (device < 0) return hipErrorInvalidDevice;
-    if (all.size() <= (size_t)device) all.resize((size_t)device + 1);
-    Device &d = all[(size_t)device];
+    Device &d = devices().try_emplace(device, Device{SwCuPool<hipStream_t, hipEvent_t>(cus), {}}).first->second;
     const int want = std::min(nwg, cus);
-    int held = 0;
-    for (const Flight &f : d.flights) held += f.cus;
-    auto retire = [&] {
-        held -= d.flights.front().cus;
-        d.spare.push_back(d.flights.front().done);
-        d.flights.pop_front();
-    };
-    while (!d.flights.empty() && hipEventQuery(d.flights.front().done) == hipSuccess) retire();
-    (void)hipGetLastError();                          // hipErrorNotReady is no error here
-    while (!d.flights.empty() && (held + want > cus || d.flights.size() >= kInFlight)) {
-        hipError_t e = hipStreamWaitEvent(s, d.flights.front().done, 0);
-        if (e != hipSuccess) return e;
-        retire();
-    }
+    hipError_t e = hipSuccess;
     hipEvent_t done;
     if (!d.spare.empty()) {
         done = d.spare.back();
         d.spare.pop_back();
-    } else {
-        hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = sw_res_launch(a, dtype, scheme, rows, exact, nw, nwg, s);
-    if (e == hipSuccess) e = hipEventRecord(done, s);
-    if (e != hipSuccess) {
-        d.spare.push_back(done);
+    } else if ((e = hipEventCreateWithFlags(&done, hipEventDisableTiming)) != hipSuccess) {
         return e;
     }
-    d.flights.push_back(Flight{done, want});
-    return hipSuccess;
+    auto drop = [&](hipEvent_t ev) { d.spare.push_back(ev); };
+    d.pool.collect([](hipEvent_t ev) { return hipEventQuery(ev) == hipSuccess; }, drop);
+    (void)hipGetLastError();                          // hipErrorNotReady is no error here
+    if (!d.pool.take(want, s, [&](hipEvent_t ev) { return (e = hipStreamWaitEvent(s, ev, 0)) == hipSuccess; }, drop)) {
+        d.spare.push_back(done);
+        return e != hipSuccess ? e : hipErrorInvalidValue;
+    }
+    e = sw_res_launch(a, dtype, scheme, rows, exact, nw, nwg, s);
+    const hipError_t r = hipEventRecord(done, s);     // (also where the launch failed: behind what it waited for)
+    if (r == hipSuccess) {
+        d.pool.lend(want, s, done);
+    } else {
+        d.pool.put_back(want);
+        d.spare.push_back(done);
+    }
+    return e != hipSuccess ? e : r;
+}
+
+// For the tests (not in sw.h): n launches in turn, none of which ends, of nwg[i] workgroups on stream[i], on a device
+// of `cus` compute units; waits[i * n + k] is set where launch i is ordered behind launch k.  Returns the most shares
+// kept at a time.
+extern "C" int sw_internal_admission(int cus, int n, const int *nwg, const int *stream, unsigned char *waits) {
+    SwCuPool<int, int> pool(cus);
+    size_t most = 0;
+    for (int i = 0; i < n; ++i) {
+        const int want = std::min(nwg[i], cus);
+        if (!pool.take(want, stream[i], [&](int k) { return waits[i * n + k] = 1, true; }, [](int) {})) return -1;
+        pool.lend(want, stream[i], i);
+        most = std::max(most, pool.shares());
+    }
+    return (int)most;
 }
