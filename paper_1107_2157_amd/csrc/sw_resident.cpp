@@ -189,6 +189,13 @@ hipError_t sw_res_launch(const SwResArgs &a, int dtype, int scheme, int rows, bo
 
 namespace {
 
+// Compute units a launch of nwg workgroups takes: workgroups go to the XCDs
+// in turn, so a launch has one more on some of them than on others, and the
+// units it holds must cover it on each (9 and 247 workgroups are 2 and 31 on
+// the first of 8 XCDs of 32 units).
+constexpr int kXcds = 8;
+int units_of(int nwg, int cus) { return std::min(((int64_t)nwg + kXcds - 1) / kXcds * kXcds, (int64_t)cus); }
+
 struct Device {
     SwCuPool<hipStream_t, hipEvent_t> pool;
     std::vector<hipEvent_t> spare;
@@ -205,7 +212,7 @@ hipError_t sw_res_launch_admitted(const SwResArgs &a, int dtype, int scheme, int
                                   int device, int cus, hipStream_t s) {
     std::lock_guard<std::mutex> hold(g_mutex);
     Device &d = devices().try_emplace(device, Device{SwCuPool<hipStream_t, hipEvent_t>(cus), {}}).first->second;
-    const int want = std::min(nwg, cus);
+    const int want = units_of(nwg, cus);
     hipError_t e = hipSuccess;
     hipEvent_t done;
     if (!d.spare.empty()) {
@@ -239,7 +246,7 @@ extern "C" int sw_internal_admission(int cus, int n, const int *nwg, const int *
     SwCuPool<int, int> pool(cus);
     size_t most = 0;
     for (int i = 0; i < n; ++i) {
-        const int want = std::min(nwg[i], cus);
+        const int want = units_of(nwg[i], cus);
         if (!pool.take(want, stream[i], [&](int k) { return waits[i * n + k] = 1, true; }, [](int) {})) return -1;
         pool.lend(want, stream[i], i);
         most = std::max(most, pool.shares());

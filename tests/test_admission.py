@@ -67,3 +67,12 @@ def test_shares_stay_bounded():
     n = 400
     nwg = [rng.choice([1, 2, 3, 40]) for _ in range(n)]
     admit(64, nwg, [rng.randint(0, 99) for _ in range(n)])
+
+
+@pytest.mark.parametrize("nwg,stream", CASES + [([12, 244], [0, 1]), ([9, 247], [0, 1])])
+def test_concurrent_launches_fit_each_xcd(nwg, stream):
+    """Workgroup i of a launch runs on XCD i % 8, of 32 compute units each."""
+    before = admit(256, nwg, stream)
+    for c in together(before):
+        for x in range(8):
+            assert sum((min(nwg[i], 256) - x + 7) // 8 for i in c) <= 32, (c, [nwg[i] for i in c], x)
