@@ -16,15 +16,6 @@ template <typename Stream, typename Event> class SwCuPool {
   public:
     explicit SwCuPool(int cus) : free_(cus) { shares_.reserve((size_t)cus + 1); }   // (never grown: a share has a unit)
 
-    // Units of launches for which done(event) holds are free again; drop(event) is told of each.
-    template <typename Done, typename Drop> void collect(Done done, Drop drop) {
-        for (size_t k = 0; k < shares_.size();) {
-            if (!done(shares_[k].event)) { ++k; continue; }
-            free_ += shares_[k].cus;
-            drop(shares_[k].event);
-            shares_.erase(shares_.begin() + k);
-        }
-    }
     // Takes `want` units (at most all there are) for a launch on `stream`: those of launches before it on the stream
     // (behind which it is anyway), then free ones, then those of other launches, oldest first.  wait(event) orders the
     // stream behind a launch whose units are taken; false if that failed, and nothing is taken.

@@ -222,8 +222,6 @@ hipError_t sw_res_launch_admitted(const SwResArgs &a, int dtype, int scheme, int
         return e;
     }
     auto drop = [&](hipEvent_t ev) { d.spare.push_back(ev); };
-    d.pool.collect([](hipEvent_t ev) { return hipEventQuery(ev) == hipSuccess; }, drop);
-    (void)hipGetLastError();                          // hipErrorNotReady is no error here
     if (!d.pool.take(want, s, [&](hipEvent_t ev) { return (e = hipStreamWaitEvent(s, ev, 0)) == hipSuccess; }, drop)) {
         d.spare.push_back(done);
         return e != hipSuccess ? e : hipErrorInvalidValue;
