@@ -299,7 +299,8 @@ sw_status sw_batch_fill_halo(sw_batch *batch, void *stream);
  * when nsteps is odd.  With the default tuning (or the batch autotuner's)
  * most batches advance in one launch for the whole call, each grid held on
  * chip while it is stepped, largest grids first (as sw_step; bitwise the same
- * results).  Otherwise a batch of 4 M cells or more per step advances as
+ * results), where the call has enough steps for that to be the faster form
+ * (one for small batches, about ten for the largest).  Otherwise a batch of 4 M cells or more per step advances as
  * two chains of grids, the second on a stream the batch owns (default
  * priority), forked from `stream` after the call's first launches and joined
  * back into it at the end: work enqueued on `stream` afterwards sees the

@@ -54,7 +54,7 @@ struct sw_batch {
     bool use_graph = true;
     // the resident time loop (res_nwg > 0 where it is the faster form): teams,
     // the workgroups' teams, control and exchange words in one block
-    int res_nwg = 0, res_rows = 0, res_nw = 0, cus = 0;
+    int res_nwg = 0, res_rows = 0, res_nw = 0, res_from = 1, cus = 0;
     bool res_exact = false;
     bool searched = false;            // the tuning is the autotuner's choice
     char *res_mem = nullptr;
@@ -290,7 +290,8 @@ hipError_t build_resident(sw_batch *b) {
         ny[i] = b->grids[i].ny;
         pitch[i] = b->lay[i].pitch;
     }
-    if (!sw_res_plan_batch((int)b->opts.dtype, b->n, nx.data(), ny.data(), pitch.data(), b->cus, &plan)) return hipSuccess;
+    if (!sw_res_plan_batch((int)b->opts.dtype, (int)b->opts.scheme, b->n, nx.data(), ny.data(), pitch.data(), b->cus, &plan))
+        return hipSuccess;
     const size_t teams = align_up(plan.teams.size() * sizeof(SwResTeam));
     const size_t wgs = align_up(plan.wg_team.size() * sizeof(int32_t));
     const size_t ctl = align_up((size_t)b->n * sizeof(SwResCtl));
@@ -308,16 +309,17 @@ hipError_t build_resident(sw_batch *b) {
     b->res_rows = plan.rows;
     b->res_nw = plan.nw;
     b->res_exact = plan.exact;
+    b->res_from = plan.from_steps;
     b->res_nwg = (int)plan.wg_team.size();
     return hipSuccess;
 }
 
 // Whether a call runs as one resident launch: the default tuning or the
 // autotuner's (a shape set by the caller is run as asked), a batch that is
-// cut for it, and a stream that is not being captured.
-bool resident_call(const sw_batch *b, hipStream_t s) {
+// cut for it, enough steps, and a stream that is not being captured.
+bool resident_call(const sw_batch *b, int nsteps, hipStream_t s) {
     static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
-    if (!b->res_nwg || (!b->searched && std::memcmp(&b->tuning, &dflt, sizeof dflt) != 0)) return false;
+    if (!b->res_nwg || nsteps < b->res_from || (!b->searched && std::memcmp(&b->tuning, &dflt, sizeof dflt) != 0)) return false;
     return !sw_res_capturing(s);
 }
 
@@ -627,7 +629,7 @@ sw_status sw_batch_step(sw_batch *b, int32_t nsteps, void *stream) {
     if ((st = resolve(b, b->tuning, &r)) != SW_OK) return st;
     if ((st = build_tiles(b, r)) != SW_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    if (resident_call(b, s)) {
+    if (resident_call(b, nsteps, s)) {
         if ((st = resident_steps(b, nsteps, s)) != SW_OK) return st;
     } else if (!b->use_graph) {
         if ((st = enqueue(b, r, nsteps, b->cur, s)) != SW_OK) return st;
@@ -888,5 +890,9 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
     if (best_out) sw_batch_get_tuning(b, best_out);
     return SW_OK;
 }
+
+// For the tests (not in sw.h): whether a call of nsteps steps on a stream
+// that is not being captured is one resident launch.
+int sw_internal_batch_resident(const sw_batch *b, int nsteps) { return b && resident_call(b, nsteps, nullptr); }
 
 }  // extern "C"

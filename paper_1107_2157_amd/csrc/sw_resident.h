@@ -99,9 +99,11 @@ struct SwResBatchPlan {
     uint64_t nwords;
     int rows, nw;
     bool exact;
+    int from_steps;                    // calls of fewer steps are faster as per-step launches
 };
 // False where the per-step launches are the faster form, or a grid does not fit.
-bool sw_res_plan_batch(int dtype, int n, const int *nx, const int *ny, const int64_t *pitch, int cus, SwResBatchPlan *out);
+bool sw_res_plan_batch(int dtype, int scheme, int n, const int *nx, const int *ny, const int64_t *pitch, int cus,
+                       SwResBatchPlan *out);
 
 bool sw_res_capturing(hipStream_t s);   // whether the stream is under capture (or cannot be asked)
 
