@@ -142,8 +142,8 @@ sw_status sw_fill_halo(sw_ctx *ctx, const sw_state *state, void *stream);
  * sw_sync_status); the run continues on garbage.
  * With the default tuning (or a fused shape that sw_autotune picked), a grid
  * whose state fits the registers of the device (about 5 million cells in
- * SW_F32, 2 million in SW_F64) is advanced by one launch for the whole call,
- * its state held on chip; buf[cur ^ 1] is then left as it was unless nsteps is
+ * SW_F32, 2 million in SW_F64) is advanced by one launch for the whole call (a
+ * launch per 20 ms or so of a long one), its state held on chip; buf[cur ^ 1] is then left as it was unless nsteps is
  * odd.  Otherwise, and on a stream under capture, one launch per step.  The
  * results are bitwise the same.  Launches of the first kind wait for each
  * other where they would not fit the device together, also across streams.
@@ -297,7 +297,8 @@ sw_status sw_batch_view(const sw_batch *batch, int32_t i, sw_state *view, sw_lay
 sw_status sw_batch_fill_halo(sw_batch *batch, void *stream);
 /* Async: advance every grid by nsteps (>= 0); the current buffer flips
  * when nsteps is odd.  With the default tuning (or the batch autotuner's)
- * most batches advance in one launch for the whole call, each grid held on
+ * most batches advance in one launch for the whole call (a launch per 100 ms
+ * or so of a long one), each grid held on
  * chip while it is stepped, largest grids first (as sw_step; bitwise the same
  * results), where the call has enough steps for that to be the faster form
  * (one for small batches, about ten for the largest).  Otherwise a batch of 4 M cells or more per step advances as

@@ -284,7 +284,6 @@ sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStre
     a.words = ctx->res_words;
     a.ctl = ctx->res_ctl;
     a.cur = state->cur;
-    a.nsteps = nsteps;
     a.bc_x = (int32_t)ctx->opts.bc_x;
     a.bc_y = (int32_t)ctx->opts.bc_y;
     a.g = ctx->g;
@@ -296,9 +295,13 @@ sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStre
     a.rdy = sw_res_exact_inverse(ctx->dy);
     a.poll_first = kResPollFirst;
     a.patience = ctx->patience;
-    SW_HIP(sw_res_launch_admitted(a, (int)ctx->opts.dtype, (int)ctx->opts.scheme, ctx->res.rows,
-                                  ctx->res.exact, ctx->res.nw,
-                                  ctx->res.team.nwg, ctx->device, ctx->cus, s));
+    for (int left = nsteps; left > 0; left -= a.nsteps) {
+        a.nsteps = sw_res_next_steps(left, ctx->res.most_steps);
+        SW_HIP(sw_res_launch_admitted(a, (int)ctx->opts.dtype, (int)ctx->opts.scheme, ctx->res.rows,
+                                      ctx->res.exact, ctx->res.nw,
+                                      ctx->res.team.nwg, ctx->device, ctx->cus, s));
+        a.cur ^= a.nsteps & 1;
+    }
     return SW_OK;
 }
 
@@ -668,6 +671,8 @@ bool sw_ctx_searched(const sw_ctx *ctx) { return ctx->searched; }
 // ticks a workgroup of this context waits for its team; below 0 it does not
 // wait at all, so that the team always gives up.
 extern "C" void sw_internal_ctx_patience(sw_ctx *ctx, long long ticks) { ctx->patience = ticks; }
+// The same of the steps of one launch.
+extern "C" void sw_internal_ctx_most_steps(sw_ctx *ctx, int steps) { ctx->res.most_steps = steps; }
 
 void sw_ctx_drop_graphs(sw_ctx *ctx) {
     if (ctx) drop_graphs(ctx);

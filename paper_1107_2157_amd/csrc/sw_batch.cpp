@@ -54,8 +54,9 @@ struct sw_batch {
     bool use_graph = true;
     // the resident time loop (res_nwg > 0 where it is the faster form): teams,
     // the workgroups' teams, control and exchange words in one block
-    int res_nwg = 0, res_rows = 0, res_nw = 0, res_from = 1, cus = 0;
+    int res_nwg = 0, res_rows = 0, res_nw = 0, res_from = 1, res_most = 1, cus = 0;
     bool res_exact = false;
+    int64_t patience = kResPatience;
     bool searched = false;            // the tuning is the autotuner's choice
     char *res_mem = nullptr;
     SwResTeam *res_teams = nullptr;
@@ -310,6 +311,7 @@ hipError_t build_resident(sw_batch *b) {
     b->res_nw = plan.nw;
     b->res_exact = plan.exact;
     b->res_from = plan.from_steps;
+    b->res_most = plan.most_steps;
     b->res_nwg = (int)plan.wg_team.size();
     return hipSuccess;
 }
@@ -332,7 +334,6 @@ sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
     a.words = b->res_words;
     a.ctl = b->res_ctl;
     a.cur = b->cur;
-    a.nsteps = nsteps;
     a.bc_x = (int)b->opts.bc_x;
     a.bc_y = (int)b->opts.bc_y;
     a.g = b->g;
@@ -343,9 +344,13 @@ sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
     a.rdx = sw_res_exact_inverse(b->dx);
     a.rdy = sw_res_exact_inverse(b->dy);
     a.poll_first = kResPollFirst;
-    a.patience = kResPatience;
-    BHIP(sw_res_launch_admitted(a, (int)b->opts.dtype, (int)b->opts.scheme, b->res_rows, b->res_exact, b->res_nw,
-                                b->res_nwg, b->device, b->cus, s));
+    a.patience = b->patience;
+    for (int left = nsteps; left > 0; left -= a.nsteps) {
+        a.nsteps = sw_res_next_steps(left, b->res_most);
+        BHIP(sw_res_launch_admitted(a, (int)b->opts.dtype, (int)b->opts.scheme, b->res_rows, b->res_exact, b->res_nw,
+                                    b->res_nwg, b->device, b->cus, s));
+        a.cur ^= a.nsteps & 1;
+    }
     return SW_OK;
 }
 
@@ -891,8 +896,13 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
     return SW_OK;
 }
 
-// For the tests (not in sw.h): whether a call of nsteps steps on a stream
-// that is not being captured is one resident launch.
+// For the tests (not in sw.h): the patience of the batch's resident launches
+// (as sw_internal_ctx_patience) and the steps of one, and whether a call of
+// nsteps steps on a stream that is not being captured takes them.
+void sw_internal_batch_limits(sw_batch *b, long long ticks, int steps) {
+    b->patience = ticks;
+    b->res_most = steps;
+}
 int sw_internal_batch_resident(const sw_batch *b, int nsteps) { return b && resident_call(b, nsteps, nullptr); }
 
 }  // extern "C"

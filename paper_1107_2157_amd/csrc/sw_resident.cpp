@@ -64,6 +64,8 @@ bool sw_res_cut(int dtype, int nx, int ny, int64_t pitch, int nw, int max_rows, 
     return true;
 }
 
+static double us_per_row(int dtype) { return dtype ? 0.37 : 0.135; }   // of a wave that has its SIMD to itself
+
 // The cut with the least work per step on a CU's busiest SIMD, in rows: the
 // patches' rows and about 1.5 more each for the halo rows and the exchange,
 // times the waves that share the SIMD, which run at 1 / 1.35 and 1 / 1.1 of
@@ -89,6 +91,8 @@ bool sw_res_plan(int dtype, int nx, int ny, int64_t pitch, int cus, SwResPlan *o
             }
         }
     }
+    // (time per step as sw_res_plan_batch estimates it)
+    if (found) out->most_steps = (int)std::max(64.0, kResLaunchUs / (us_per_row(dtype) * best + 2.5));
     return found;
 }
 
@@ -192,7 +196,7 @@ bool sw_res_plan_batch(int dtype, int scheme, int n, const int *nx, const int *n
         int teams = 0;
         auto close = [&] {
             static const double at[5] = {0.0, 1.35, 2.2, 3.7, 5.2};
-            us += (dtype ? 0.37 : 0.135) * at[(used + cus - 1) / cus] * (p.rows + 1.5) + 2.5 / teams;
+            us += us_per_row(dtype) * at[(used + cus - 1) / cus] * (p.rows + 1.5) + 2.5 / teams;
             used = teams = 0;
         };
         for (int g : order) {
@@ -209,20 +213,29 @@ bool sw_res_plan_batch(int dtype, int scheme, int n, const int *nx, const int *n
     }
     if (!found) return false;
     out->from_steps = batch_from_steps(dtype, scheme, n, nx, ny, cus, best, *out);
+    out->most_steps = (int)std::max(64.0, kResBatchLaunchUs / best);
     return out->from_steps < INT_MAX;
 }
 
 // For the tests (not in sw.h): the cut of a batch.  out: rows, waves per
-// workgroup, workgroups, those of the largest team, from_steps; returns 0
-// where the per-step launches are kept.
+// workgroup, workgroups, those of the largest team, from_steps, most_steps;
+// returns 0 where the per-step launches are kept.
 extern "C" int sw_internal_plan_batch(int dtype, int scheme, int n, const int *nx, const int *ny, int cus, int *out) {
     SwResBatchPlan p;
     const std::vector<int64_t> pitch((size_t)n, 0);
     if (!sw_res_plan_batch(dtype, scheme, n, nx, ny, pitch.data(), cus, &p)) return 0;
     int team = 0;
     for (const SwResTeam &t : p.teams) team = std::max(team, t.nwg);
-    const int got[5] = {p.rows, p.nw, (int)p.wg_team.size(), team, p.from_steps};
-    std::copy(got, got + 5, out);
+    const int got[6] = {p.rows, p.nw, (int)p.wg_team.size(), team, p.from_steps, p.most_steps};
+    std::copy(got, got + 6, out);
+    return 1;
+}
+// The same of a single grid: rows, waves per workgroup, workgroups, most_steps.
+extern "C" int sw_internal_plan_grid(int dtype, int nx, int ny, int cus, int *out) {
+    SwResPlan p;
+    if (!sw_res_plan(dtype, nx, ny, 0, cus, &p)) return 0;
+    const int got[4] = {p.rows, p.nw, p.team.nwg, p.most_steps};
+    std::copy(got, got + 4, out);
     return 1;
 }
 

@@ -55,9 +55,17 @@ struct SwResPlan {
     bool exact;              // every active wave has rows or rows - 1, and there is an instance for that
     SwResTeam team;          // wg0 and words are the caller's
     uint64_t nwords;         // exchange words (8 bytes)
+    int most_steps;          // steps of one launch at most (sw_res_plan)
 };
 
 constexpr int64_t kResPatience = 500000000;   // 5 s in ticks of the 100 MHz clock
+// Estimated time of one launch at most (us); longer calls are several
+// launches.  In a batch of more workgroups than fit a team waits for the teams
+// before it, a whole launch at worst, and must not run out of patience; and
+// where a team gives up, what one workgroup then does alone is a launch, not
+// the call.  A launch costs 20 us beside its steps, in a batch a reading and
+// writing of all states: longer there.
+constexpr double kResLaunchUs = 20e3, kResBatchLaunchUs = 100e3;
 constexpr int kResFlagWords = 4;   // exchange words from one workgroup's flag to the next (32 bytes)
 constexpr int kResPollFirst = 9;   // 128 cycles each: 0.5 us
 constexpr int kResStrip = 62;      // most columns of a strip
@@ -100,10 +108,18 @@ struct SwResBatchPlan {
     int rows, nw;
     bool exact;
     int from_steps;                    // calls of fewer steps are faster as per-step launches
+    int most_steps;                    // steps of one launch at most
 };
 // False where the per-step launches are the faster form, or a grid does not fit.
 bool sw_res_plan_batch(int dtype, int scheme, int n, const int *nx, const int *ny, const int64_t *pitch, int cus,
                        SwResBatchPlan *out);
+
+// Steps of the next launch of a call with `left` steps to go: as many launches
+// as `most` asks for, of about equal length.
+inline int sw_res_next_steps(int left, int most) {
+    const int launches = (int)(((int64_t)left + most - 1) / most);
+    return (int)(((int64_t)left + launches - 1) / launches);
+}
 
 bool sw_res_capturing(hipStream_t s);   // whether the stream is under capture (or cannot be asked)
 

@@ -1,0 +1,104 @@
+"""Limits of the resident loop: calls of several launches, teams that give up."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_1107_2157_amd import ics, sw
+from swtest import G, announce
+
+pytestmark = pytest.mark.gpu
+
+
+def pair(nx, ny, seed, **how):
+    """A solver at its default tuning and one that takes a launch per step, at the same state."""
+    a, b = sw.Solver(nx, ny, g=G, **how), sw.Solver(nx, ny, g=G, **how)
+    b.set_variant(sw.VARIANT_FUSED)
+    u = ics.random_state(nx, ny, seed=seed)
+    a.set_state(*u)
+    b.set_state(*u)
+    return a, b
+
+
+def batches(sides, **how):
+    a, b = (sw.Batch(sides, g=G, **how) for _ in range(2))
+    b.set_tuning(variant=2)
+    for i, (nx, ny) in enumerate(sides):
+        u = ics.random_state(nx, ny, seed=i)
+        a.set_state(i, *u)
+        b.set_state(i, *u)
+    return a, b
+
+
+def same(a, b, what):
+    assert a.sync_status() == b.sync_status(), what
+    assert a.state.cur == b.state.cur
+    for k, (x, y) in enumerate(zip(a.get_state(halo=True), b.get_state(halo=True))):
+        assert torch.equal(x, y), f"{what}: field {k} differs"
+
+
+def same_batch(a, b, what):
+    assert a.sync_status() == b.sync_status(), what
+    for i in range(a.n):
+        for x, y in zip(a.get_state(i, halo=True), b.get_state(i, halo=True)):
+            assert torch.equal(x, y), f"{what}: grid {i}"
+
+
+def batch_limits(a, patience, steps):
+    f = sw.lib().sw_internal_batch_limits
+    f.argtypes = [ctypes.c_void_p, ctypes.c_longlong, ctypes.c_int]
+    f.restype = None
+    f(a.handle, patience, steps)
+
+
+def is_resident(a, steps):
+    f = sw.lib().sw_internal_batch_resident
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    return f(a.handle, steps) == 1
+
+
+PATIENCE = 500_000_000
+
+
+@pytest.mark.parametrize("how", [dict(dtype="f32"), dict(dtype="f64", scheme=sw.SCHEME_TRANSVERSE, bc_x=sw.PERIODIC),
+                                 dict(dtype="f32", cfl=0.0, dt_fixed=0.01)])
+def test_call_of_several_launches(how):
+    announce(f"resident call of several launches: 190x70 {how}")
+    a, b = pair(190, 70, 4, **how)
+    f = sw.lib().sw_internal_ctx_most_steps
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    f.restype = None
+    f(a.ctx, 3)
+    for steps in (11, 3, 4, 1):                # 3 + 3 + 3 + 2, 3, 2 + 2, 1
+        a.step(steps)
+        b.step(steps)
+        same(a, b, f"{steps} steps")
+
+
+def test_batch_call_of_several_launches():
+    sides = [(64, 64), (130, 130), (320, 320), (5, 40)]
+    announce(f"resident batch call of several launches: {sides}")
+    a, b = batches(sides, dtype="f32")
+    batch_limits(a, PATIENCE, 4)
+    for steps in (9, 8, 5):
+        assert is_resident(a, steps)
+        a.step(steps)
+        b.step(steps)
+        same_batch(a, b, f"{steps} steps")
+
+
+def test_batch_teams_that_give_up():
+    """Every team's last workgroup does the steps of its grid alone: the same bits."""
+    sides = [(130, 130), (64, 48), (200, 150)]
+    announce(f"resident batch given up: {sides}")
+    a, b = batches(sides, dtype="f32", bc_y=sw.PERIODIC)
+    batch_limits(a, -1, 64)
+    for steps in (3, 4):
+        assert is_resident(a, steps)
+        a.step(steps)
+        b.step(steps)
+        same_batch(a, b, f"given up, {steps} steps")
+    batch_limits(a, PATIENCE, 64)
+    a.step(5)
+    b.step(5)
+    same_batch(a, b, "after launches that were given up")

@@ -9,10 +9,10 @@ F32, F64 = 0, 1
 
 
 def plan_batch(dtype, scheme, sides, cus=256):
-    """(rows, waves per workgroup, workgroups, largest team, from_steps) or None."""
+    """(rows, waves per workgroup, workgroups, largest team, from_steps, most_steps) or None."""
     n = len(sides)
     ints = ctypes.c_int * n
-    out = (ctypes.c_int * 5)()
+    out = (ctypes.c_int * 6)()
     f = sw.lib().sw_internal_plan_batch
     if not f(dtype, scheme, n, ints(*[s[0] for s in sides]), ints(*[s[1] for s in sides]), cus, out):
         return None
@@ -44,3 +44,28 @@ def test_short_batch_calls_take_the_faster_form(dtype, scheme, sides, ratio):
     for steps, r in ratio.items():
         if not 0.88 < r < 1.12:
             assert (steps >= p[4]) == (r < 1.0), (steps, r, p)
+
+
+def plan_grid(dtype, nx, ny, cus=256):
+    """(rows, waves per workgroup, workgroups, most_steps) or None."""
+    out = (ctypes.c_int * 4)()
+    return tuple(out) if sw.lib().sw_internal_plan_grid(dtype, nx, ny, cus, out) else None
+
+
+# us per step, measured on MI355X
+@pytest.mark.parametrize("dtype,scheme,sides,us", [
+    (F32, 0, [(256, 256)] * 256, 54.5), (F32, 0, [(1024, 1024)] * 16, 52.3), (F32, 0, [(64, 64)] * 32, 2.9),
+    (F32, 1, [(1024, 1024)] * 16, 64.0), (F64, 0, [(512, 512)] * 60, 99.0), (F64, 1, [(512, 512)] * 60, 128.5)])
+def test_batch_launches_stay_far_below_the_patience(dtype, scheme, sides, us):
+    """A team that does not fit at first waits for whole launches of the teams
+    before it, at most one launch's time; it gives up after 5 s."""
+    p = plan_batch(dtype, scheme, sides)
+    assert p[5] >= 64 and p[5] * us < 0.5e6, p
+
+
+@pytest.mark.parametrize("dtype,nx,ny,us", [(F32, 64, 48, 2.6), (F32, 1024, 1024, 5.9), (F32, 2048, 2048, 14.8),
+                                            (F64, 128, 128, 3.0), (F64, 1024, 1024, 10.7)])
+def test_grid_launches_are_short(dtype, nx, ny, us):
+    """What one workgroup does alone where a team gives up is a launch, not the call."""
+    p = plan_grid(dtype, nx, ny)
+    assert p[3] >= 64 and p[3] * us < 0.1e6, p
