@@ -143,10 +143,12 @@ sw_status sw_fill_halo(sw_ctx *ctx, const sw_state *state, void *stream);
  * With the default tuning (or a fused shape that sw_autotune picked), a grid
  * whose state fits the registers of the device (about 5 million cells in
  * SW_F32, 2 million in SW_F64) is advanced by one launch for the whole call (a
- * launch per 20 ms or so of a long one), its state held on chip; buf[cur ^ 1] is then left as it was unless nsteps is
- * odd.  Otherwise, and on a stream under capture, one launch per step.  The
- * results are bitwise the same.  Launches of the first kind wait for each
- * other where they would not fit the device together, also across streams.
+ * launch per 20 ms or so of a long one), its state held on chip; buf[cur ^ 1]
+ * is then left as it was unless a launch ends there.  Otherwise, and on a
+ * stream under capture or with a mask of fewer compute units than the device
+ * has, one launch per step.  The results are bitwise the same.  Launches of
+ * the first kind wait for each other where they would not fit the device
+ * together, also across streams.
  * Errors (synchronous): SW_EINVAL, SW_EHIP, SW_ENOMEM (workspace of
  * variant 4 or 5), SW_ENOTSUP (a variant the options exclude). */
 sw_status sw_step(sw_ctx *ctx, sw_state *state, int32_t nsteps, void *stream);

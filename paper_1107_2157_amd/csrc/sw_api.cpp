@@ -266,12 +266,12 @@ void drop_graphs(sw_ctx *ctx) {
 
 // Whether this call runs as one resident launch: the default tuning or a
 // fused shape that the autotuner picked (one set by the caller is run as
-// asked), a grid that fits the device, and a stream that is not being captured.
+// asked), a grid that fits the device, and a stream that takes such launches.
 bool resident_call(const sw_ctx *ctx, hipStream_t s) {
     static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
     if (!ctx->res_ok) return false;
     if (!(ctx->searched && ctx->tuning.variant == 2) && std::memcmp(&ctx->tuning, &dflt, sizeof dflt) != 0) return false;
-    return !sw_res_capturing(s);
+    return sw_res_stream_ok(s, ctx->cus);
 }
 
 sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStream_t s) {
@@ -671,7 +671,11 @@ bool sw_ctx_searched(const sw_ctx *ctx) { return ctx->searched; }
 // ticks a workgroup of this context waits for its team; below 0 it does not
 // wait at all, so that the team always gives up.
 extern "C" void sw_internal_ctx_patience(sw_ctx *ctx, long long ticks) { ctx->patience = ticks; }
-// The same of the steps of one launch.
+// Whether a call on the stream takes resident launches.
+extern "C" int sw_internal_ctx_resident(sw_ctx *ctx, void *stream) {
+    return use_device(ctx) == SW_OK && resident_call(ctx, (hipStream_t)stream);
+}
+// As sw_internal_ctx_patience, the steps of one launch.
 extern "C" void sw_internal_ctx_most_steps(sw_ctx *ctx, int steps) { ctx->res.most_steps = steps; }
 
 void sw_ctx_drop_graphs(sw_ctx *ctx) {

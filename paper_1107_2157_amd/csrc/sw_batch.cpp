@@ -318,11 +318,11 @@ hipError_t build_resident(sw_batch *b) {
 
 // Whether a call runs as one resident launch: the default tuning or the
 // autotuner's (a shape set by the caller is run as asked), a batch that is
-// cut for it, enough steps, and a stream that is not being captured.
+// cut for it, enough steps, and a stream that takes such launches.
 bool resident_call(const sw_batch *b, int nsteps, hipStream_t s) {
     static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
     if (!b->res_nwg || nsteps < b->res_from || (!b->searched && std::memcmp(&b->tuning, &dflt, sizeof dflt) != 0)) return false;
-    return !sw_res_capturing(s);
+    return sw_res_stream_ok(s, b->cus);
 }
 
 sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
@@ -898,11 +898,13 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
 
 // For the tests (not in sw.h): the patience of the batch's resident launches
 // (as sw_internal_ctx_patience) and the steps of one, and whether a call of
-// nsteps steps on a stream that is not being captured takes them.
+// nsteps steps on the stream takes them.
 void sw_internal_batch_limits(sw_batch *b, long long ticks, int steps) {
     b->patience = ticks;
     b->res_most = steps;
 }
-int sw_internal_batch_resident(const sw_batch *b, int nsteps) { return b && resident_call(b, nsteps, nullptr); }
+int sw_internal_batch_resident(const sw_batch *b, int nsteps, void *stream) {
+    return check_bound(b) == SW_OK && resident_call(b, nsteps, (hipStream_t)stream);
+}
 
 }  // extern "C"

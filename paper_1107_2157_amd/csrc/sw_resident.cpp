@@ -239,13 +239,25 @@ extern "C" int sw_internal_plan_grid(int dtype, int nx, int ny, int cus, int *ou
     return 1;
 }
 
-bool sw_res_capturing(hipStream_t s) {
+bool sw_res_stream_ok(hipStream_t s, int cus) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
         (void)hipGetLastError();
-        return true;
+        return false;
     }
-    return cs != hipStreamCaptureStatusNone;
+    if (cs != hipStreamCaptureStatusNone) return false;
+    if ((uintptr_t)s <= (uintptr_t)hipStreamPerThread) return true;   // a default stream: no handle to ask, and no mask
+    constexpr int kWords = 32;
+    uint32_t mask[kWords] = {};
+    const int words = (cus + 31) / 32;
+    if (words > kWords) return false;
+    if (hipExtStreamGetCUMask(s, (uint32_t)words, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int on = 0;
+    for (int k = 0; k < words; ++k) on += __builtin_popcount(mask[k]);
+    return on >= cus;
 }
 
 hipError_t sw_res_launch_f32(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);

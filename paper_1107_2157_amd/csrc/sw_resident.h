@@ -121,7 +121,11 @@ inline int sw_res_next_steps(int left, int most) {
     return (int)(((int64_t)left + launches - 1) / launches);
 }
 
-bool sw_res_capturing(hipStream_t s);   // whether the stream is under capture (or cannot be asked)
+// Whether resident launches may go to the stream: it is not under capture (or
+// cannot be asked), and its kernels may use every compute unit (a team cut for
+// the device would never find room on a stream created with a mask of fewer,
+// and wait out its patience each call).
+bool sw_res_stream_ok(hipStream_t s, int cus);
 
 // 1 / x where that is exact for every product with it, else 0.
 inline double sw_res_exact_inverse(double x) {

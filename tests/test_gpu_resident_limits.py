@@ -53,8 +53,8 @@ def batch_limits(a, patience, steps):
 
 def is_resident(a, steps):
     f = sw.lib().sw_internal_batch_resident
-    f.argtypes = [ctypes.c_void_p, ctypes.c_int]
-    return f(a.handle, steps) == 1
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    return f(a.handle, steps, None) == 1
 
 
 PATIENCE = 500_000_000

@@ -112,3 +112,41 @@ def test_uneven_grids_on_many_streams():
             b.step(1 + k % 7)
         same(a, b, "uneven grids")
     assert took < 4.0, f"{took:.1f} s: a team waited out its patience (5 s)"
+
+
+def test_stream_with_a_mask_of_compute_units():
+    """A stream whose kernels may use half of the device takes the per-step
+    launches: a team cut for the whole device would never come together."""
+    announce("steps on a stream with a mask of compute units")
+    a, b = pair(700, 640, 8)
+    batch, ref = (sw.Batch([(256, 256)] * 16, g=G) for _ in range(2))
+    ref.set_tuning(variant=2)
+    u = ics.random_state(256, 256, seed=9)
+    for i in range(16):
+        batch.set_state(i, *u)
+        ref.set_state(i, *u)
+    h = hip()
+    words = (torch.cuda.get_device_properties(0).multi_processor_count + 31) // 32
+    some = (ctypes.c_uint32 * words)(*[0xffffffff if k < words // 2 else 0 for k in range(words)])
+    every = (ctypes.c_uint32 * words)(*[0xffffffff] * words)
+    grid_route, batch_route = sw.lib().sw_internal_ctx_resident, sw.lib().sw_internal_batch_resident
+    grid_route.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    batch_route.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    torch.cuda.synchronize()
+    for mask, resident in ((some, 0), (every, 1)):
+        s = ctypes.c_void_p()
+        assert h.hipExtStreamCreateWithCUMask(ctypes.byref(s), words, mask) == 0
+        assert grid_route(a.ctx, s) == resident and batch_route(batch.handle, 9, s) == resident
+        stream = torch.cuda.ExternalStream(s.value)
+        a.step(5, stream=stream)
+        batch.step(9, stream=stream)
+        assert h.hipStreamSynchronize(s) == 0
+        assert h.hipStreamDestroy(s) == 0
+    for s in (None, torch.cuda.Stream().cuda_stream):
+        assert grid_route(a.ctx, s) == 1
+    b.step(10)
+    same(a, b, "masked stream")
+    ref.step(18)
+    assert batch.sync_status() == ref.sync_status()
+    for i in range(16):
+        assert torch.equal(batch.interior(i, 0), ref.interior(i, 0))
