@@ -148,7 +148,10 @@ sw_status sw_fill_halo(sw_ctx *ctx, const sw_state *state, void *stream);
  * stream under capture or with a mask of fewer compute units than the device
  * has, one launch per step.  The results are bitwise the same.  Launches of
  * the first kind wait for each other where they would not fit the device
- * together, also across streams.
+ * together, also across streams.  Where other processes' work keeps such a
+ * launch's workgroups from starting for 5 s, one of them takes all of its
+ * steps, which is much slower; the sw_sync_status (sw_batch_sync_status) that
+ * sees this puts the context (batch) on per-step launches for good.
  * Errors (synchronous): SW_EINVAL, SW_EHIP, SW_ENOMEM (workspace of
  * variant 4 or 5), SW_ENOTSUP (a variant the options exclude). */
 sw_status sw_step(sw_ctx *ctx, sw_state *state, int32_t nsteps, void *stream);

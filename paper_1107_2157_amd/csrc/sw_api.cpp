@@ -635,6 +635,9 @@ sw_status sw_sync_status(sw_ctx *ctx, void *stream, double *t, double *last_dt, 
     if (t) *t = h.t;
     if (last_dt) *last_dt = h.last_dt;
     if (steps) *steps = h.steps;
+    // The device is not this process's alone: a team waited out its patience and one workgroup did a launch's steps.
+    // Per-step launches only run slower there.  (Not where a test asked for no patience.)
+    if (h.alone && ctx->patience >= 0) ctx->res_ok = false;
     if (h.unstable) return fail(SW_EUNSTABLE, "a step produced h <= 0 or a non-finite value");
     return SW_OK;
 }

@@ -715,6 +715,7 @@ sw_status sw_batch_sync_status(sw_batch *b, void *stream, double *t, int64_t *st
         if (steps) steps[i] = h[i].steps;
         if (unstable) unstable[i] = (int32_t)h[i].unstable;
         any |= h[i].unstable != 0;
+        if (h[i].alone && b->patience >= 0) b->res_nwg = 0;   // (as sw_sync_status: per-step launches from here on)
     }
     if (any) return sw_fail(SW_EUNSTABLE, "batch: a grid produced h <= 0 or a non-finite value");
     return SW_OK;

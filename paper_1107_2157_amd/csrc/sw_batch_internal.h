@@ -17,7 +17,7 @@ struct SwBatchScalars {
     double last_dt;
     long long steps;
     unsigned int unstable;
-    unsigned int pad;
+    unsigned int alone;       // as SwScalars::alone
 };
 
 // Per-grid descriptor: plane pointers at interior cell (0, 0) of both buffers.

@@ -17,7 +17,7 @@ struct SwScalars {
     double last_dt;           // dt of the last step
     long long steps;          // steps taken
     unsigned int unstable;    // sticky: some step produced h <= 0 or non-finite
-    unsigned int pad;
+    unsigned int alone;       // resident launches whose team did not come together
 };
 
 // One launch's view of the state and the parameters of the scheme.  Plane

@@ -779,10 +779,10 @@ __global__ __launch_bounds__(64 * NW) void k_resident(const SwResArgs a) {
         if (a.teams) {
             SwBatchScalars *sc = a.bsc + ti;
             if (anybad) atomicOr(&sc->unstable, 1u);
-            if (books) { sc->t = time; sc->last_dt = last_dt; sc->steps += a.nsteps; }
+            if (books) { sc->t = time; sc->last_dt = last_dt; sc->steps += a.nsteps; sc->alone += !go; }
         } else {
             if (anybad) atomicOr(&a.sc->unstable, 1u);
-            if (books) { a.sc->t = time; a.sc->last_dt = last_dt; a.sc->steps += a.nsteps; }
+            if (books) { a.sc->t = time; a.sc->last_dt = last_dt; a.sc->steps += a.nsteps; a.sc->alone += !go; }
         }
     }
     if (last_one && threadIdx.x == 0) {

@@ -102,3 +102,37 @@ def test_batch_teams_that_give_up():
     a.step(5)
     b.step(5)
     same_batch(a, b, "after launches that were given up")
+
+
+def test_per_step_launches_after_a_team_gave_up():
+    """A team that gives up shows that the device is shared: once the status
+    call has seen it, calls take the per-step launches."""
+    announce("per-step launches after a team gave up")
+    a, b = pair(190, 70, 5, dtype="f64")
+    patience = sw.lib().sw_internal_ctx_patience
+    patience.argtypes = [ctypes.c_void_p, ctypes.c_longlong]
+    patience.restype = None
+    route = sw.lib().sw_internal_ctx_resident
+    route.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    batch, ref = batches([(64, 48), (130, 130)], dtype="f32")
+    a.step(2)
+    batch.step(2)
+    a.sync_status()
+    batch.sync_status()
+    assert route(a.ctx, None) == 1 and is_resident(batch, 4)
+    patience(a.ctx, -1)
+    batch_limits(batch, -1, 64)
+    a.step(3)
+    batch.step(3)
+    torch.cuda.synchronize()
+    patience(a.ctx, PATIENCE)
+    batch_limits(batch, PATIENCE, 64)
+    a.sync_status()
+    batch.sync_status()
+    assert route(a.ctx, None) == 0 and not is_resident(batch, 4)
+    a.step(4)
+    batch.step(4)
+    b.step(9)
+    ref.step(9)
+    same(a, b, "after giving up")
+    same_batch(batch, ref, "after giving up")
