@@ -245,9 +245,14 @@ typedef struct {
     int32_t order;      /* fused: tile order: 0 row-block-major per XCD, 1 vertically grouped per XCD, 2 plain */
 } sw_tuning;
 
-/* Errors: SW_EINVAL for a NULL argument or an unsupported combination. */
+/* A shape set here is run as asked, one launch per step, unless it is the one
+ * sw_get_tuning reports for the library's own choice (the default's, or
+ * sw_autotune's): saved, and set again, that leaves sw_step free to advance the
+ * grid in one launch per call.
+ * Errors: SW_EINVAL for a NULL argument or an unsupported combination. */
 sw_status sw_set_tuning(sw_ctx *ctx, const sw_tuning *tuning);
-/* The tuning sw_step will use, with defaults resolved. */
+/* The tuning with defaults resolved: the launch shape of sw_step's per-step
+ * launches. */
 sw_status sw_get_tuning(const sw_ctx *ctx, sw_tuning *out);
 
 /* 1 (default): sw_step replays one hipGraph per (nsteps, current buffer,

@@ -41,7 +41,8 @@ struct sw_ctx {
     // the resident time loop, where the grid fits the device (res_ok): its cut,
     // exchange words and control (behind the scalars, in the same block)
     bool res_ok = false;
-    bool searched = false;   // the tuning is the autotuner's choice
+    sw_tuning found{};       // the autotuner's choice (variant 0: none yet)
+    bool own = true;         // the tuning is the library's own choice (own_choice)
     int64_t patience = kResPatience;
     SwResPlan res{};
     int cus = 0;
@@ -264,14 +265,11 @@ void drop_graphs(sw_ctx *ctx) {
     ctx->graphs.clear();
 }
 
-// Whether this call runs as one resident launch: the default tuning or a
-// fused shape that the autotuner picked (one set by the caller is run as
-// asked), a grid that fits the device, and a stream that takes such launches.
+// Whether this call runs as resident launches: the library's own choice of a
+// fused shape (one set by the caller is run as asked), a grid that fits the
+// device, and a stream that takes such launches.
 bool resident_call(const sw_ctx *ctx, hipStream_t s) {
-    static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
-    if (!ctx->res_ok) return false;
-    if (!(ctx->searched && ctx->tuning.variant == 2) && std::memcmp(&ctx->tuning, &dflt, sizeof dflt) != 0) return false;
-    return sw_res_stream_ok(s, ctx->cus);
+    return ctx->res_ok && ctx->own && (ctx->tuning.variant == 0 || ctx->tuning.variant == 2) && sw_res_stream_ok(s, ctx->cus);
 }
 
 sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStream_t s) {
@@ -513,6 +511,32 @@ sw_status resolve_tuning(const sw_ctx *ctx, const sw_tuning &in, SwTuning *out) 
                     out->rows, (long long)ctx->layout.pitch);
     return SW_OK;
 }
+
+// The tuning as sw_get_tuning reports it.
+bool reported(const sw_ctx *ctx, const sw_tuning &t, sw_tuning *out) {
+    SwTuning r;
+    if (resolve_tuning(ctx, t, &r) != SW_OK) return false;
+    *out = sw_tuning{r.variant, r.rows, r.vec, r.minw, r.pd, r.order};
+    return true;
+}
+
+// Whether the tuning is the library's own: none set, or the default's or the
+// autotuner's as sw_get_tuning reports it (a program that saves what it got,
+// tries another and sets it again asks for no launch shape of its own).
+bool own_choice(const sw_ctx *ctx) {
+    const sw_tuning none{0, 0, 0, 0, 0, 0};
+    auto is = [&](const sw_tuning &t) {
+        sw_tuning r;
+        return std::memcmp(&ctx->tuning, &t, sizeof t) == 0 ||
+               (reported(ctx, t, &r) && std::memcmp(&ctx->tuning, &r, sizeof r) == 0);
+    };
+    return is(none) || (ctx->found.variant && is(ctx->found));
+}
+
+void apply_tuning(sw_ctx *ctx, const sw_tuning &t) {
+    ctx->tuning = t;
+    ctx->own = own_choice(ctx);
+}
 }  // namespace
 
 sw_status sw_set_variant(sw_ctx *ctx, int32_t variant) {
@@ -523,8 +547,7 @@ sw_status sw_set_variant(sw_ctx *ctx, int32_t variant) {
     SwTuning r;
     sw_status st = resolve_tuning(ctx, t, &r);
     if (st != SW_OK && st != SW_ENOTSUP) return st;
-    ctx->tuning = t;
-    ctx->searched = false;
+    apply_tuning(ctx, t);
     return SW_OK;
 }
 
@@ -533,8 +556,7 @@ sw_status sw_set_tuning(sw_ctx *ctx, const sw_tuning *tuning) {
     SwTuning r;
     sw_status st = resolve_tuning(ctx, *tuning, &r);
     if (st != SW_OK) return st;
-    ctx->tuning = *tuning;
-    ctx->searched = false;
+    apply_tuning(ctx, *tuning);
     return SW_OK;
 }
 
@@ -667,8 +689,24 @@ sw_status sw_reset_time(sw_ctx *ctx, void *stream) {
 
 bool sw_ctx_use_graph(const sw_ctx *ctx) { return ctx && ctx->use_graph; }
 
-void sw_ctx_set_searched(sw_ctx *ctx, bool searched) { ctx->searched = searched; }
-bool sw_ctx_searched(const sw_ctx *ctx) { return ctx->searched; }
+sw_tuning sw_ctx_tuning(const sw_ctx *ctx) { return ctx->tuning; }
+void sw_ctx_put_tuning(sw_ctx *ctx, const sw_tuning &t, bool own) {
+    ctx->tuning = t;
+    ctx->own = own;
+}
+bool sw_ctx_own_tuning(const sw_ctx *ctx) { return ctx->own; }
+sw_status sw_ctx_try_tuning(sw_ctx *ctx, const sw_tuning &t) {
+    sw_status st = sw_set_tuning(ctx, &t);
+    if (st == SW_OK) ctx->own = false;
+    return st;
+}
+sw_status sw_ctx_found_tuning(sw_ctx *ctx, const sw_tuning &t) {
+    sw_status st = sw_set_tuning(ctx, &t);
+    if (st != SW_OK) return st;
+    ctx->found = t;
+    ctx->own = true;
+    return SW_OK;
+}
 
 // For the tests of the resident loop's way out (not in sw.h): the 100 MHz
 // ticks a workgroup of this context waits for its team; below 0 it does not

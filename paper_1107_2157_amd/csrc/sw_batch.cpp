@@ -57,7 +57,8 @@ struct sw_batch {
     int res_nwg = 0, res_rows = 0, res_nw = 0, res_from = 1, res_most = 1, cus = 0;
     bool res_exact = false;
     int64_t patience = kResPatience;
-    bool searched = false;            // the tuning is the autotuner's choice
+    sw_tuning found{};                // the autotuner's choice (variant 0: none yet)
+    bool own = true;                  // the tuning is the library's own choice (own_choice)
     char *res_mem = nullptr;
     SwResTeam *res_teams = nullptr;
     int32_t *res_wg_team = nullptr;
@@ -316,13 +317,11 @@ hipError_t build_resident(sw_batch *b) {
     return hipSuccess;
 }
 
-// Whether a call runs as one resident launch: the default tuning or the
-// autotuner's (a shape set by the caller is run as asked), a batch that is
-// cut for it, enough steps, and a stream that takes such launches.
+// Whether a call runs as resident launches: the library's own choice of a
+// launch shape (one set by the caller is run as asked), a batch that is cut
+// for it, enough steps, and a stream that takes such launches.
 bool resident_call(const sw_batch *b, int nsteps, hipStream_t s) {
-    static const sw_tuning dflt{0, 0, 0, 0, 0, 0};
-    if (!b->res_nwg || nsteps < b->res_from || (!b->searched && std::memcmp(&b->tuning, &dflt, sizeof dflt) != 0)) return false;
-    return sw_res_stream_ok(s, b->cus);
+    return b->res_nwg && b->own && nsteps >= b->res_from && sw_res_stream_ok(s, b->cus);
 }
 
 sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
@@ -355,6 +354,17 @@ sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
 }
 
 bool same_tuning(const sw_tuning &x, const sw_tuning &y) { return std::memcmp(&x, &y, sizeof x) == 0; }
+
+// Whether the tuning is the library's own: none set, or the default's or the
+// autotuner's as sw_batch_get_tuning reports it.
+bool own_choice(const sw_batch *b) {
+    auto is = [&](const sw_tuning &t) {
+        Resolved r;
+        return same_tuning(b->tuning, t) ||
+               (resolve(b, t, &r) == SW_OK && same_tuning(b->tuning, sw_tuning{2, r.rows, r.vec, r.minw, r.pd, r.order}));
+    };
+    return is(sw_tuning{}) || (b->found.variant && is(b->found));
+}
 
 sw_status check_bound(const sw_batch *b) {
     if (!b) return sw_fail(SW_EINVAL, "batch: NULL");
@@ -441,7 +451,8 @@ int sw_batch_internal_clone(const sw_batch *src, sw_batch **out, void **arena) {
     sw_status st = sw_batch_create(src->n, src->grids.data(), halo, src->g, src->dx, &src->opts, &c);
     if (st != SW_OK) return st;
     c->tuning = src->tuning;
-    c->searched = src->searched;
+    c->found = src->found;
+    c->own = src->own;
     hipError_t e = hipMalloc(arena, 2 * c->region);
     if (e != hipSuccess) {
         sw_batch_destroy(c);
@@ -585,7 +596,7 @@ sw_status sw_batch_set_tuning(sw_batch *b, const sw_tuning *t) {
     if (st != SW_OK) return st;
     const bool had = resolve(b, b->tuning, &prev) == SW_OK;
     b->tuning = *t;
-    b->searched = false;
+    b->own = own_choice(b);
     // any change of the launch shape renews the generation, so rollouts
     // captured by a surrogate with the old shape are captured anew (the tile
     // table below renews it too when rows, vec or order change)
@@ -783,7 +794,8 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
             }
         }
         if (found && sw_batch_set_tuning(b, &hit) == SW_OK) {
-            b->searched = true;
+            b->found = hit;
+            b->own = true;
             if (best_out) sw_batch_get_tuning(b, best_out);
             return SW_OK;
         }
@@ -800,7 +812,7 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
                         for (int order = 0; order <= 2; ++order) cands.push_back(sw_tuning{2, rows, vecs[vi], occ, pd, order});
     const bool graph0 = b->use_graph;
     const sw_tuning prev = b->tuning;
-    const bool prev_searched = b->searched;
+    const bool prev_own = b->own;
     const int cur0 = b->cur;
     void *backup = nullptr, *sbackup = nullptr;
     const size_t sbytes = (size_t)b->n * sizeof(SwBatchScalars);
@@ -854,6 +866,7 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
     double best_us = 1e300;
     for (size_t i = 0; i < cands.size() && he == hipSuccess; ++i) {
         if (sw_batch_set_tuning(b, &cands[i]) != SW_OK) continue;
+        b->own = false;                      // the launches of this shape
         if ((he = warm(1, 1 + steps)) != hipSuccess) break;
         float m1 = 1e30f, mk = 1e30f;
         for (int rep = 0; rep < 2 && he == hipSuccess; ++rep) {
@@ -882,12 +895,13 @@ sw_status sw_batch_autotune(sw_batch *b, int32_t steps_per_trial, const char *ca
     b->use_graph = graph0;
     if (he != hipSuccess || best_us >= 1e300) {
         sw_batch_set_tuning(b, &prev);
-        b->searched = prev_searched;
+        b->own = prev_own;
         return he != hipSuccess ? sw_fail(SW_EHIP, "batch_autotune: %s", hipGetErrorString(he))
                                 : sw_fail(SW_ENOTSUP, "batch_autotune: no candidate ran");
     }
     sw_batch_set_tuning(b, &best);
-    b->searched = true;
+    b->found = best;
+    b->own = true;
     if (cache_path && *cache_path) {
         std::ofstream f(cache_path, std::ios::app);
         f << key << " " << best.variant << " " << best.rows << " " << best.vec << " " << best.occupancy << " "

@@ -78,8 +78,11 @@ sw_status sw_ctx_describe(const sw_ctx *ctx, sw_grid *grid, sw_opts *opts, sw_la
                           size_t *scalars_bytes);
 
 bool sw_ctx_use_graph(const sw_ctx *ctx);
-void sw_ctx_set_searched(sw_ctx *ctx, bool searched);   // the tuning is this search's choice, not the caller's
-bool sw_ctx_searched(const sw_ctx *ctx);
+sw_tuning sw_ctx_tuning(const sw_ctx *ctx);                          // as it was set,
+bool sw_ctx_own_tuning(const sw_ctx *ctx);                           // whether it is the library's own choice,
+void sw_ctx_put_tuning(sw_ctx *ctx, const sw_tuning &t, bool own);   // and both put back
+sw_status sw_ctx_try_tuning(sw_ctx *ctx, const sw_tuning &t);        // a launch shape to be timed
+sw_status sw_ctx_found_tuning(sw_ctx *ctx, const sw_tuning &t);      // the search's choice
 void sw_ctx_drop_graphs(sw_ctx *ctx);   // the context's captured graphs (none may be in flight)
 
 extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per_trial, const char *cache_path,
@@ -98,8 +101,7 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
     const std::string key = tune_key(opts.dtype, opts.scheme, grid.nx, grid.ny, opts.dt_fixed > 0, device);
 
     sw_tuning best{};
-    if (cache_lookup(cache_path, key, &best) && sw_set_tuning(ctx, &best) == SW_OK) {
-        sw_ctx_set_searched(ctx, true);
+    if (cache_lookup(cache_path, key, &best) && sw_ctx_found_tuning(ctx, best) == SW_OK) {
         if (best_out) sw_get_tuning(ctx, best_out);
         return SW_OK;
     }
@@ -153,9 +155,8 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
         return hipMemcpyAsync(scal, scal_backup, scal_bytes, hipMemcpyDeviceToDevice, s);
     };
 
-    sw_tuning prev{};
-    sw_get_tuning(ctx, &prev);
-    const bool prev_searched = sw_ctx_searched(ctx);
+    const sw_tuning prev = sw_ctx_tuning(ctx);
+    const bool prev_own = sw_ctx_own_tuning(ctx);
     // trials replay graphs, as sw_step runs: eager launches would time the
     // host's launch rate on small grids; each shape's two call lengths are
     // captured in an untimed warm-up first
@@ -167,7 +168,7 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
     if (he == hipSuccess) he = hipEventCreate(&e1);
     if (he == hipSuccess) he = save();
     for (size_t i = 0; i < cands.size() && he == hipSuccess; ++i) {
-        if (sw_set_tuning(ctx, &cands[i]) != SW_OK) continue;
+        if (sw_ctx_try_tuning(ctx, cands[i]) != SW_OK) continue;
         // room for this shape's two graphs (the cache evicts all when full);
         // the previous trial ended with an event synchronisation
         sw_ctx_drop_graphs(ctx);
@@ -215,17 +216,14 @@ extern "C" sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per
     (void)hipFree(scal_backup);
     sw_set_graph(ctx, graph ? 1 : 0);
     if (he != hipSuccess) {
-        sw_set_tuning(ctx, &prev);
-        sw_ctx_set_searched(ctx, prev_searched);
+        sw_ctx_put_tuning(ctx, prev, prev_own);
         return SW_EHIP;
     }
     if (best_us >= 1e300) {
-        sw_set_tuning(ctx, &prev);
-        sw_ctx_set_searched(ctx, prev_searched);
+        sw_ctx_put_tuning(ctx, prev, prev_own);
         return SW_ENOTSUP;
     }
-    sw_set_tuning(ctx, &best);
-    sw_ctx_set_searched(ctx, true);
+    sw_ctx_found_tuning(ctx, best);
     cache_store(cache_path, key, best, best_us);
     if (best_out) sw_get_tuning(ctx, best_out);
     return SW_OK;
