@@ -265,7 +265,8 @@ sw_status sw_set_graph(sw_ctx *ctx, int32_t enable);
  * it.  buf[cur], its halo and the context's time/flags are saved first and
  * restored afterwards, so the simulation is left where it was.  Allocates
  * (and frees) a temporary copy of one buffer of device memory.  With a
- * fixed dt the blocked kernel is among the candidates.  If cache_path is
+ * fixed dt the blocked kernel is among the candidates; it is picked where it is
+ * also faster than the one launch per call of sw_step.  If cache_path is
  * non-NULL, a cached choice for the same (GPU, dtype, scheme, grid, fixed or
  * CFL dt) is used without timing, and new choices are appended there.
  * best may be NULL.  Synchronises the stream.

@@ -689,6 +689,7 @@ sw_status sw_reset_time(sw_ctx *ctx, void *stream) {
 
 bool sw_ctx_use_graph(const sw_ctx *ctx) { return ctx && ctx->use_graph; }
 
+bool sw_ctx_resident(const sw_ctx *ctx, hipStream_t s) { return resident_call(ctx, s); }
 sw_tuning sw_ctx_tuning(const sw_ctx *ctx) { return ctx->tuning; }
 void sw_ctx_put_tuning(sw_ctx *ctx, const sw_tuning &t, bool own) {
     ctx->tuning = t;
