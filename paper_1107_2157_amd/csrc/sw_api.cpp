@@ -403,8 +403,15 @@ sw_status sw_create(sw_grid grid, sw_halo halo, double g, double dx, const sw_op
     size_t bytes = sc_bytes;
     if (e == hipSuccess) {
         c->res_ok = sw_res_plan((int)o.dtype, grid.nx, grid.ny, lay.pitch, c->cus, &c->res);
-        if (c->res_ok) bytes += 256 + (size_t)c->res.nwords * 8;
-        e = hipMalloc((void **)&c->sc, bytes);
+        if (c->res_ok) {
+            bytes += 256 + (size_t)c->res.nwords * 8;
+            e = sw_res_alloc((void **)&c->sc, bytes);
+            if (e == hipSuccess && !c->sc) {
+                c->res_ok = false;
+                bytes = sc_bytes;
+            }
+        }
+        if (e == hipSuccess && !c->sc) e = hipMalloc((void **)&c->sc, bytes);
     }
     if (e == hipSuccess) e = hipMemset(c->sc, 0, bytes);
     if (e == hipSuccess && c->res_ok) {

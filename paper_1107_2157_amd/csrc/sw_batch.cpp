@@ -282,7 +282,7 @@ sw_status enqueue(const sw_batch *b, const Resolved &r, int nsteps, int cur, hip
 }
 
 // Cut every grid for the resident loop and lay out its tables; res_nwg stays 0
-// where the per-step launches are kept.
+// where the per-step launches are kept, or there is no memory for them.
 hipError_t build_resident(sw_batch *b) {
     SwResBatchPlan plan;
     std::vector<int> nx(b->n), ny(b->n);
@@ -297,8 +297,8 @@ hipError_t build_resident(sw_batch *b) {
     const size_t teams = align_up(plan.teams.size() * sizeof(SwResTeam));
     const size_t wgs = align_up(plan.wg_team.size() * sizeof(int32_t));
     const size_t ctl = align_up((size_t)b->n * sizeof(SwResCtl));
-    hipError_t e = hipMalloc((void **)&b->res_mem, teams + wgs + ctl + plan.nwords * 8);
-    if (e != hipSuccess) return e;
+    hipError_t e = sw_res_alloc((void **)&b->res_mem, teams + wgs + ctl + plan.nwords * 8);
+    if (e != hipSuccess || !b->res_mem) return e;
     b->res_teams = (SwResTeam *)b->res_mem;
     b->res_wg_team = (int32_t *)(b->res_mem + teams);
     b->res_ctl = (SwResCtl *)(b->res_mem + teams + wgs);

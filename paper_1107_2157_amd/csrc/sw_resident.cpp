@@ -260,6 +260,22 @@ bool sw_res_stream_ok(hipStream_t s, int cus) {
     return on >= cus;
 }
 
+// For the tests (not in sw.h): the calling thread's next sw_res_alloc finds no
+// memory.
+static thread_local bool t_deny = false;
+extern "C" void sw_internal_deny_alloc() { t_deny = true; }
+
+hipError_t sw_res_alloc(void **p, size_t bytes) {
+    *p = nullptr;
+    const bool deny = t_deny;
+    t_deny = false;
+    const hipError_t e = deny ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return hipSuccess;
+}
+
 hipError_t sw_res_launch_f32(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
 hipError_t sw_res_launch_f64(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);
 hipError_t sw_res_launch_f32_tr(const SwResArgs &a, int rows, bool exact, int nw, int nwg, hipStream_t s);

@@ -133,6 +133,10 @@ inline double sw_res_exact_inverse(double x) {
     return std::frexp(x, &e) == 0.5 && e > -1000 && e < 1000 ? 1.0 / x : 0.0;
 }
 
+// Device memory that a context or batch can do without (it then takes the
+// per-step launches): null where there is not enough.
+hipError_t sw_res_alloc(void **p, size_t bytes);
+
 // Launch nwg workgroups of nw waves.  rows: the most rows of any wave; exact:
 // every active wave has rows or rows - 1.
 hipError_t sw_res_launch(const SwResArgs &a, int dtype, int scheme, int rows, bool exact, int nw, int nwg, hipStream_t s);

@@ -136,3 +136,28 @@ def test_per_step_launches_after_a_team_gave_up():
     ref.step(9)
     same(a, b, "after giving up")
     same_batch(batch, ref, "after giving up")
+
+
+def test_no_memory_for_the_exchange():
+    """A context or batch without memory for the exchange words is created all
+    the same, and takes the per-step launches."""
+    announce("no memory for the exchange words")
+    deny = sw.lib().sw_internal_deny_alloc
+    deny.argtypes, deny.restype = [], None
+    route = sw.lib().sw_internal_ctx_resident
+    route.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    deny()
+    a, b = pair(190, 70, 5, dtype="f32")
+    assert route(a.ctx, None) == 0
+    deny()
+    batch, ref = batches([(64, 48), (130, 130)], dtype="f64")
+    assert not is_resident(batch, 40)
+    for steps in (2, 5):
+        a.step(steps)
+        b.step(steps)
+        same(a, b, f"{steps} steps")
+        batch.step(steps)
+        ref.step(steps)
+        same_batch(batch, ref, f"{steps} steps")
+    c, _ = pair(190, 70, 5, dtype="f32")
+    assert route(c.ctx, None) == 1
