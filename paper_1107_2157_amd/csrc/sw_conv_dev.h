@@ -4,6 +4,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstdint>
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -92,20 +95,30 @@ __device__ __forceinline__ void conv_row(const __bf16 *T, const int off[3], cons
 
 // Rows per run of a kernel that gives each workgroup a run of rows of one of
 // B images of H rows (`slots` workgroups at a time, `extra` steps beside a
-// run's rows): as few rounds as possible.  *nseg: runs per image.
-inline int conv_run_rows(int B, int H, int64_t slots, int extra, int *nseg) {
-    int best = H;
+// run's rows): the runs, at least four rows each, that take the fewest steps.
+// *nseg: runs per image; *trials (may be null): run lengths looked at.  For
+// each number of rounds the shortest runs that need no more are the best, and
+// a number of rounds costs `extra` steps each beside the rows themselves: the
+// search ends where that alone exceeds the best (a few dozen lengths, where
+// trying all down to four rows took milliseconds a launch for tall images).
+inline int conv_run_rows(int B, int H, int64_t slots, int extra, int *nseg, int *trials = nullptr) {
+    const int most = std::max(1, (H + 3) / 4);                // runs per image
+    int best = H, n = 0;
     *nseg = 1;
     int64_t best_cost = -1;
-    for (int k = 1; k <= H; ++k) {
-        const int rows = (H + k - 1) / k, segs = (H + rows - 1) / rows;
+    for (int64_t rounds = (B + slots - 1) / slots;; ++rounds) {
+        if (best_cost >= 0 && rounds * extra + (int64_t)B * H / slots >= best_cost) break;
+        const int64_t k = std::min<int64_t>(rounds * slots / B, most);
+        const int rows = (int)((H + k - 1) / k), segs = (H + rows - 1) / rows;
         const int64_t cost = ((int64_t)B * segs + slots - 1) / slots * (rows + extra);
+        ++n;
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = rows;
             *nseg = segs;
         }
-        if (rows <= 4) break;
+        if (k == most) break;
     }
+    if (trials) *trials = n;
     return best;
 }

@@ -369,3 +369,8 @@ hipError_t sw_conv_pair(const SwPairArgs &a, int pair, hipStream_t s) {
     if (!a.x) return hipErrorInvalidValue;
     return pair == SW_PAIR_OUT ? launch_mids<RESID, true>(a, s) : launch_mids<RESID, false>(a, s);
 }
+
+// For the tests (not in sw.h).
+extern "C" int sw_internal_run_rows(int B, int H, long long slots, int extra, int *nseg, int *trials) {
+    return conv_run_rows(B, H, slots, extra, nseg, trials);
+}
