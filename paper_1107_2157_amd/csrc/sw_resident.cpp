@@ -218,16 +218,16 @@ bool sw_res_plan_batch(int dtype, int scheme, int n, const int *nx, const int *n
 }
 
 // For the tests (not in sw.h): the cut of a batch.  out: rows, waves per
-// workgroup, workgroups, those of the largest team, from_steps, most_steps;
-// returns 0 where the per-step launches are kept.
+// workgroup, workgroups, those of the largest team, from_steps, most_steps,
+// exact; returns 0 where the per-step launches are kept.
 extern "C" int sw_internal_plan_batch(int dtype, int scheme, int n, const int *nx, const int *ny, int cus, int *out) {
     SwResBatchPlan p;
     const std::vector<int64_t> pitch((size_t)n, 0);
     if (!sw_res_plan_batch(dtype, scheme, n, nx, ny, pitch.data(), cus, &p)) return 0;
     int team = 0;
     for (const SwResTeam &t : p.teams) team = std::max(team, t.nwg);
-    const int got[6] = {p.rows, p.nw, (int)p.wg_team.size(), team, p.from_steps, p.most_steps};
-    std::copy(got, got + 6, out);
+    const int got[7] = {p.rows, p.nw, (int)p.wg_team.size(), team, p.from_steps, p.most_steps, p.exact};
+    std::copy(got, got + 7, out);
     return 1;
 }
 // The same of a single grid: rows, waves per workgroup, workgroups, most_steps.

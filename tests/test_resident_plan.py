@@ -9,10 +9,10 @@ F32, F64 = 0, 1
 
 
 def plan_batch(dtype, scheme, sides, cus=256):
-    """(rows, waves per workgroup, workgroups, largest team, from_steps, most_steps) or None."""
+    """(rows, waves per workgroup, workgroups, largest team, from_steps, most_steps, exact) or None."""
     n = len(sides)
     ints = ctypes.c_int * n
-    out = (ctypes.c_int * 6)()
+    out = (ctypes.c_int * 7)()
     f = sw.lib().sw_internal_plan_batch
     if not f(dtype, scheme, n, ints(*[s[0] for s in sides]), ints(*[s[1] for s in sides]), cus, out):
         return None
