@@ -292,6 +292,7 @@ sw_status resident_steps(sw_ctx *ctx, const sw_state *state, int nsteps, hipStre
     a.rdx = sw_res_exact_inverse(ctx->dx);
     a.rdy = sw_res_exact_inverse(ctx->dy);
     a.poll_first = kResPollFirst;
+    a.poll_next = kResPollNext;
     a.patience = ctx->patience;
     for (int left = nsteps; left > 0; left -= a.nsteps) {
         a.nsteps = sw_res_next_steps(left, ctx->res.most_steps);

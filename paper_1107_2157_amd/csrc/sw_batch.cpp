@@ -343,6 +343,7 @@ sw_status resident_steps(const sw_batch *b, int nsteps, hipStream_t s) {
     a.rdx = sw_res_exact_inverse(b->dx);
     a.rdy = sw_res_exact_inverse(b->dy);
     a.poll_first = kResPollFirst;
+    a.poll_next = kResPollNext;
     a.patience = b->patience;
     for (int left = nsteps; left > 0; left -= a.nsteps) {
         a.nsteps = sw_res_next_steps(left, b->res_most);

@@ -68,6 +68,10 @@ constexpr int64_t kResPatience = 500000000;   // 5 s in ticks of the 100 MHz clo
 constexpr double kResLaunchUs = 20e3, kResBatchLaunchUs = 100e3;
 constexpr int kResFlagWords = 4;   // exchange words from one workgroup's flag to the next (32 bytes)
 constexpr int kResPollFirst = 9;   // 128 cycles each: 0.5 us
+// Between polls: none is the fastest, but for the few cycles that asking takes
+// (dam break of 128^2 FP64, 100 steps: 319.0 us; without the question 320.0;
+// 1024^2 FP32: 562.5 / 565.3, with 64 cycles 565.5).
+constexpr int kResPollNext = 0;
 constexpr int kResStrip = 62;      // most columns of a strip
 constexpr int kResRows = 16;       // most rows of a wave with 16 (FP32) or 8 (FP64) waves to a CU
 constexpr int kResRoomy = 10;      // FP32 patches from this height take twice the registers where nw <= 8

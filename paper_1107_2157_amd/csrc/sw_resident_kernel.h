@@ -830,7 +830,7 @@ hipError_t launch_rows(const SwResArgs &a, int rows, bool exact, int nw, int nwg
         if (roomy) return rows <= 20 ? launch<T, 20, TR, 8, false>(a, nw, nwg, s)
                                      : launch<T, kResRowsTall, TR, 8, false>(a, nw, nwg, s);
     }
-    if (rows <= kResRows) return launch<T, kResRows, TR, NW, false>(a, nw, nwg, s);
+    if constexpr (sizeof(T) == 8) return launch<T, kResRows, TR, NW, false>(a, nw, nwg, s);   // (FP32 with 16 waves: exact cuts alone)
     return hipErrorInvalidValue;
 }
 

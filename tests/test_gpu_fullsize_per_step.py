@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 def test_batch_of_512_grids_per_step_against_whole_grid_oracle():
     """512 grids, sides 64 to 1024, 40 steps with a CFL time step each: the
     smallest, the largest and a random grid, within the bounds the resident
-    form is held to (1e-4 of each field's scale, 1e-5 of the time)."""
+    form is held to (1e-5 of each field's scale and of the time)."""
     k = 40
     sides = ics.batch_sides(512)
     announce(f"batch 512 grids, per-step launches, {k} steps, whole-grid oracle on 3 grids")
@@ -39,4 +39,4 @@ def test_batch_of_512_grids_per_step_against_whole_grid_oracle():
         H, U, V, t_ref = oracle.run(*states[i], k, g=G)
         err = rel_maxnorm(b.get_state(i), [H[1:-1, 1:-1], U[1:-1, 1:-1], V[1:-1, 1:-1]])
         print(f"grid {i} ({sides[i]}^2): rel max-norm {err:.2e}")
-        assert steps[i] == k and abs(t[i] - t_ref) <= 1e-5 * t_ref and err <= 1e-4
+        assert steps[i] == k and abs(t[i] - t_ref) <= 1e-5 * t_ref and err <= 1e-5
