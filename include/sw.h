@@ -120,8 +120,10 @@ sw_status sw_layout_query(sw_grid grid, sw_dtype dtype, sw_layout *out);
  * opts may be NULL: SW_F32, reflective walls, paper scheme, dy = dx, cfl 0.5.
  * halo must be {1, 1, 1, 1} (the width the scheme needs), else SW_ENOTSUP.
  * Allocates device memory on the current device: a few kilobytes, and for
- * grids that sw_step advances in one launch (see there) about an eighth of
- * one buffer more.
+ * grids that sw_step advances in one launch (see there) the words its
+ * workgroups exchange, at most 10 MB: a sixth of one buffer at 2200^2, a
+ * quarter at 1024^2, twice a buffer below about 300 a side (done without, and
+ * advanced by a launch per step, where there is no memory for them).
  * Errors: SW_EINVAL (shape, g <= 0, dx <= 0, cfl/dt_fixed not exactly one
  * positive, unknown enum), SW_ENOTSUP, SW_ENOMEM, SW_EHIP. */
 sw_status sw_create(sw_grid grid, sw_halo halo, double g, double dx, const sw_opts *opts, sw_ctx **out);
@@ -285,13 +287,16 @@ sw_status sw_autotune(sw_ctx *ctx, sw_state *state, int32_t steps_per_trial, con
  * batches of 4 M cells or more); sw_batch_step replays the whole call as
  * hipGraph launches (captured on first use per (nsteps, buffer, tuning)).
  * The caller owns the arena (device memory); the library owns the tile
- * table, per-grid scalars, graphs, a capture stream and the second chain's
- * stream and events. */
+ * table, per-grid scalars, exchange words, graphs, a capture stream and the
+ * second chain's stream and events. */
 typedef struct sw_batch sw_batch;
 
 /* Validates every grid like sw_create (no HIP call until then), then
- * allocates the per-grid scalars.  Errors: SW_EINVAL, SW_ENOTSUP (halo),
- * SW_ENOMEM, SW_EHIP. */
+ * allocates the per-grid scalars and, for batches that advance in one launch
+ * per call, their teams' tables and exchange words (a fifth to a third of one
+ * buffer, for small batches up to twice one; done without where there is no
+ * memory for them).  Errors: SW_EINVAL, SW_ENOTSUP (halo), SW_ENOMEM,
+ * SW_EHIP. */
 sw_status sw_batch_create(int32_t n, const sw_grid *grids, sw_halo halo, double g, double dx, const sw_opts *opts,
                           sw_batch **out);
 sw_status sw_batch_destroy(sw_batch *batch);
@@ -309,8 +314,7 @@ sw_status sw_batch_fill_halo(sw_batch *batch, void *stream);
 /* Async: advance every grid by nsteps (>= 0); the current buffer flips
  * when nsteps is odd.  With the default tuning (or the batch autotuner's)
  * most batches advance in one launch for the whole call (a launch per 100 ms
- * or so of a long one), each grid held on
- * chip while it is stepped, largest grids first (as sw_step; bitwise the same
+ * or so of a long one), each grid held on chip while it is stepped, largest grids first (as sw_step; bitwise the same
  * results), where the call has enough steps for that to be the faster form
  * (one for small batches, about ten for the largest).  Otherwise a batch of 4 M cells or more per step advances as
  * two chains of grids, the second on a stream the batch owns (default

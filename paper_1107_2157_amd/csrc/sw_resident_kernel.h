@@ -223,14 +223,15 @@ __device__ __forceinline__ double uni(double v) { return __longlong_as_double(un
 
 template <int R, bool TR> constexpr int col_values() { return (3 * R + (TR ? 6 : 0) + 3) & ~3; }
 
-// What bounds it: from about a million cells the VALU issue rate (about 75
+// What bounds it: from about a million cells the VALU issue rate (70 to 80
 // instructions per row of 64 lanes and step, five of them quarter-rate
-// reciprocals and square roots: 1536^2 FP32 8.7 us a step, 270
-// Gcell-updates/s, 19.1 us as per-step launches that read and write the state);
-// below that the step's one trip of words through memory, 1.4 us of the 2.6 us
-// that a step of 64^2 takes (4.8 us as per-step launches).  1024^2 FP32 12.1
-// -> 5.9 us, 2048^2 24.5 -> 14.8, 1024^2 FP64 16.3 -> 10.7, 1531x1087 FP64
-// transverse 26.2 -> 15.8.
+// reciprocals and square roots: 1536^2 FP32 8.5 us a step, 278
+// Gcell-updates/s, 19.1 us as per-step launches that read and write the state;
+// the issue slots are 0.54 full, the rest is the exchange); below that the
+// step's one trip of words through memory, 1.4 us of the 2.6 us that a step of
+// 64^2 takes (4.8 us as per-step launches).  1024^2 FP32 12.1 -> 5.9 us, 2048^2
+// 24.5 -> 14.8, 1024^2 FP64 16.3 -> 10.7, 1531x1087 FP64 transverse 26.2 ->
+// 15.8.
 //
 // EXACT: every wave has R or R - 1 rows, so that the row above the patch
 // stands at one of two places known at compile time (otherwise 1 to R rows).

@@ -304,8 +304,8 @@ class Solver:
 
 class Batch:
     """Many independent grids advanced together (sw_batch_*): one device
-    arena (a torch uint8 tensor), one launch per step for all grids, the
-    whole call replayed as one hipGraph."""
+    arena (a torch uint8 tensor), one launch per call, or per step for all
+    grids where that is the faster form (sw_batch_step)."""
 
     def __init__(self, sides, g: float = 9.8, dx: float = 1.0, dtype="f32", bc_x: int = REFLECT,
                  bc_y: int = REFLECT, dy: float = 0.0, cfl: float = 0.5, dt_fixed: float = 0.0, device="cuda",
