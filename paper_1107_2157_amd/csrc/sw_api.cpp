@@ -533,11 +533,12 @@ bool reported(const sw_ctx *ctx, const sw_tuning &t, sw_tuning *out) {
 // tries another and sets it again asks for no launch shape of its own).
 bool own_choice(const sw_ctx *ctx) {
     const sw_tuning none{0, 0, 0, 0, 0, 0};
+    sw_tuning now = ctx->tuning;
     auto is = [&](const sw_tuning &t) {
         sw_tuning r;
-        return std::memcmp(&ctx->tuning, &t, sizeof t) == 0 ||
-               (reported(ctx, t, &r) && std::memcmp(&ctx->tuning, &r, sizeof r) == 0);
+        return std::memcmp(&now, &t, sizeof t) == 0 || (reported(ctx, t, &r) && std::memcmp(&now, &r, sizeof r) == 0);
     };
+    if (now.variant == 0 && !is(none)) (void)reported(ctx, now, &now);   // (sw_set_variant(0) leaves the other fields)
     return is(none) || (ctx->found.variant && is(ctx->found));
 }
 

@@ -60,7 +60,7 @@ def test_round_trip_of_the_autotuners_choice(make, tmp_path):
     cache = str(tmp_path / "tune.txt")
     best = s.autotune(steps_per_trial=1, cache_path=cache)
     assert resident(s)
-    other = dict(best, rows=best["rows"] * 2)
+    other = dict(best, rows=100)          # neither the default's height nor one the search tries
     s.set_tuning(**other)
     assert not resident(s)
     s.set_tuning(**best)
@@ -96,3 +96,14 @@ def test_search_with_a_fixed_dt_keeps_the_faster_form(nx, ny, dtype, tmp_path):
     assert best["variant"] == sw.VARIANT_FUSED and resident(s)
     again = sw.Solver(nx, ny, g=G, dtype=dtype, cfl=0.0, dt_fixed=0.01)
     assert again.autotune(steps_per_trial=10, cache_path=cache) == best and resident(again)
+
+
+def test_variant_0_after_a_search():
+    """Setting the variant alone leaves the other fields: the library's choice stays it."""
+    announce("variant 0 after a search")
+    s = single()
+    best = s.autotune(steps_per_trial=1)
+    s.set_variant(sw.VARIANT_AUTO)
+    assert resident(s) and s.get_tuning() == best
+    s.set_tuning(rows=100)               # neither the default's height nor one the search tries
+    assert not resident(s)
