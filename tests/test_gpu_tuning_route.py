@@ -92,10 +92,10 @@ def test_search_with_a_fixed_dt_keeps_the_faster_form(nx, ny, dtype, tmp_path):
     s = sw.Solver(nx, ny, g=G, dtype=dtype, cfl=0.0, dt_fixed=0.01)
     s.set_state(*ics.random_state(nx, ny, seed=2))
     cache = str(tmp_path / "tune.txt")
-    best = s.autotune(steps_per_trial=10, cache_path=cache)
+    best = s.autotune(steps_per_trial=40, cache_path=cache)
     assert best["variant"] == sw.VARIANT_FUSED and resident(s)
     again = sw.Solver(nx, ny, g=G, dtype=dtype, cfl=0.0, dt_fixed=0.01)
-    assert again.autotune(steps_per_trial=10, cache_path=cache) == best and resident(again)
+    assert again.autotune(steps_per_trial=40, cache_path=cache) == best and resident(again)
 
 
 def test_variant_0_after_a_search():
